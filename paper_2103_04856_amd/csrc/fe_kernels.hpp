@@ -138,9 +138,6 @@ __device__ __forceinline__ int xcd_logical_block(int linear, int total) {
   return (linear % kXcd) * (total / kXcd) + linear / kXcd;
 }
 
-// Which per-voxel bodies a sweep kernel holds (see grad_sweep).
-enum SweepBody { kBodyAny = 0, kBodyNoS = 1, kBodyFull = 2 };
-
 // What the fused sweep writes.
 enum SweepMode {
   kGrad = 0,      // dst = dF_h/du (h^3 included); partial[1] = sum of src
@@ -327,8 +324,8 @@ __device__ __forceinline__ BlockTile block_tile(const SweepArgs<T>& a) {
 // two barriers per plane suffice.
 //
 // BODY: which per-voxel body the kernel holds. kBodyAny picks it per instance
-// (a batch that mixes p symmetric in k1, k2 with others); kBodyNoS and
-// kBodyFull hold one body only, for batches whose instances all take it: a
+// (a batch that mixes p symmetric in k1, k2 with others); kBodyNoS, kBodyFull and
+// kBodyTrace hold one body only, for batches whose instances all take it: a
 // single body needs fewer registers (FP32 32 x 32 tiles: step without S~ terms
 // 81 VGPRs against 116 with both bodies; Adam 96 and 123 against 130, where
 // both bodies leave one block per CU).
@@ -353,8 +350,10 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
   // RY * RX records), written with one instruction and read with one paired
   // instruction per neighbour pair; with one (whose kernels have no registers
   // to spare for the wider reads) the four are rows of their own, in the same
-  // storage. BXY, BXZ and BYZ are single fields.
-  enum { XP = 0, YP = 2, BXY = 4, BXZ, BYZ, NFIELD };
+  // storage. BXY, BXZ and BYZ are single fields; kBodyTrace has none of them.
+  enum { XP = 0, YP = 2, BXY = 4, BXZ, BYZ, ALL_FIELDS };
+  constexpr bool kMixed = BODY != kBodyTrace;  // the body has mixed differences
+  constexpr int NFIELD = kMixed ? ALL_FIELDS : BXY;
   constexpr bool kPairs = !SP;
   constexpr bool STEP = MODE != kGrad;
 
@@ -369,6 +368,11 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
     } else {
       sx[XP][v] = gx; sx[XP + 1][v] = bxx;
       sx[YP][v] = gy; sx[YP + 1][v] = byy;
+    }
+  };
+  auto put_mixed = [&](int v, T bxy, T bxz, T byz) {
+    if constexpr (kMixed) {
+      sx[BXY][v] = bxy; sx[BXZ][v] = bxz; sx[BYZ][v] = byz;
     }
   };
   __shared__ double sred[NT / kWave][2];
@@ -473,7 +477,7 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
   // field have to spare at two blocks per compute unit).
   constexpr bool kGatherBases = sizeof(T) == 4 && !SP;
   constexpr int NSINGLE = NFIELD - BXY;
-  lds_cptr<T> gbase[kGatherBases ? NO : 1][NSINGLE];
+  lds_cptr<T> gbase[kGatherBases ? NO : 1][NSINGLE > 0 ? NSINGLE : 1];
   lds_cptr<FieldPair<T>> gxr[kGatherBases ? NO : 1], gyr[kGatherBases ? NO : 1];
   if constexpr (kGatherBases) {
 #pragma unroll
@@ -575,7 +579,7 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
         if (!zin || gx < a.box_lo[0] || gx >= a.box_hi[0] || gy < a.box_lo[1] || gy >= a.box_hi[1]) {
           ad = VoxelAdjoint<T>{};
           put_xy(v, T(0), T(0), T(0), T(0));
-          sx[BXY][v] = T(0); sx[BXZ][v] = T(0); sx[BYZ][v] = T(0);
+          put_mixed(v, T(0), T(0), T(0));
           return T(0);
         }
       }
@@ -587,14 +591,12 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
       // (a coefficient field varies per voxel: always the full body)
       auto st = [&]() { return load_stencil<T, UX>(pc, pm, pp); };
       T f;
-      if constexpr (BODY == kBodyNoS)
-        f = voxel_density_adjoint_body<true>(st(), st, pv, a.k, ad);
-      else if constexpr (BODY == kBodyFull)
-        f = voxel_density_adjoint_body<false>(st(), st, pv, a.k, ad);
+      if constexpr (BODY != kBodyAny)
+        f = voxel_density_adjoint_body<BODY>(st(), st, pv, a.k, ad);
       else
         f = voxel_density_adjoint<SP>(st(), st, pv, a.k, ad);
       put_xy(v, ad.hgx, ad.nbxx, ad.hgy, ad.nbyy);
-      sx[BXY][v] = ad.dbxy; sx[BXZ][v] = ad.dbxz; sx[BYZ][v] = ad.dbyz;
+      put_mixed(v, ad.dbxy, ad.dbxz, ad.dbyz);
       return f;
     };
     // Interior and border voxels are dealt out from one index space, so the
@@ -643,10 +645,11 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
       if (w < TX * TY) {
         const int ix = w % TX, iy = w / TX;
         const int v = (iy + 1) * RX + ix + 1;
-        const T d = T(0.5) * ((sxat(j, v, BXZ, 1) - sxat(j, v, BXZ, -1)) +
-                              (sxat(j, v, BYZ, RX) - sxat(j, v, BYZ, -RX)));
-        const T bzz = own_bzz[j], gz = own_gz[j];
-        const T gd = gz + d;
+        const T bzz = own_bzz[j];
+        T gd = own_gz[j];
+        if constexpr (kMixed)
+          gd += T(0.5) * ((sxat(j, v, BXZ, 1) - sxat(j, v, BXZ, -1)) +
+                          (sxat(j, v, BYZ, RX) - sxat(j, v, BYZ, -RX)));
         const T upn = gd + bzz;        // minus what plane p adds to output plane p-1
         const T lo = gd - bzz;         // what plane p adds to output plane p+1
         if (it >= 2 && oin[j]) {
@@ -672,11 +675,12 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
         }
         const FieldPair<T> xp1 = xat(j, v, 1), xm1 = xat(j, v, -1);
         const FieldPair<T> yp1 = yat(j, v, RX), ym1 = yat(j, v, -RX);
-        const T cin = own_c0[j]
-                      - T(2) * ((xp1.a - xm1.a) + (yp1.a - ym1.a))
-                      - ((xp1.b + xm1.b) + (yp1.b + ym1.b))
-                      - T(0.5) * ((sxat(j, v, BXY, RX + 1) - sxat(j, v, BXY, -RX + 1)) -
-                                  (sxat(j, v, BXY, RX - 1) - sxat(j, v, BXY, -RX - 1)));
+        T cin = own_c0[j]
+                - T(2) * ((xp1.a - xm1.a) + (yp1.a - ym1.a))
+                - ((xp1.b + xm1.b) + (yp1.b + ym1.b));
+        if constexpr (kMixed)
+          cin -= T(0.5) * ((sxat(j, v, BXY, RX + 1) - sxat(j, v, BXY, -RX + 1)) -
+                           (sxat(j, v, BXY, RX - 1) - sxat(j, v, BXY, -RX - 1)));
         l_pp[j] = l_prev[j];
         l_prev[j] = lo;
         c_prev[j] = cin;
@@ -851,9 +855,9 @@ __global__ __launch_bounds__(64 * NWV) void energy_sweep_cols(SweepArgs<T> a) {
   fetch(k0 + 1);
   __syncthreads();
   read_window(1, w1);
-  // the body without S~ terms where the instance has none (one uniform branch)
-  auto run = [&](auto nos_tag) {
-    constexpr bool NOS = decltype(nos_tag)::value;
+  // the instance's body (one uniform branch)
+  auto run = [&](auto body_tag) {
+    constexpr int BODY = decltype(body_tag)::value;
     auto compute = [&](const T (&m)[WR][3], const T (&c)[WR][3], const T (&pl)[WR][3]) {
       T fs = T(0);
 #pragma unroll
@@ -868,7 +872,7 @@ __global__ __launch_bounds__(64 * NWV) void energy_sweep_cols(SweepArgs<T> a) {
           s.ypzp = pl[r + 2][1]; s.ypzm = m[r + 2][1]; s.ymzp = pl[r][1]; s.ymzm = m[r][1];
           return s;
         };
-        const T f = voxel_density_body<NOS>(st(), st, prm, a.k);
+        const T f = voxel_density_body<BODY>(st(), st, prm, a.k);
         if (xin && y0 + wv * V + r < a.ny) fs += f;
       }
       acc_f += double(fs);
@@ -896,9 +900,11 @@ __global__ __launch_bounds__(64 * NWV) void energy_sweep_cols(SweepArgs<T> a) {
     }
   };
   if (has_s_terms(prm))
-    run(std::false_type{});
+    run(std::integral_constant<int, kBodyFull>{});
+  else if (has_trace_only(prm))
+    run(std::integral_constant<int, kBodyTrace>{});
   else
-    run(std::true_type{});
+    run(std::integral_constant<int, kBodyNoS>{});
   write_partials<NT>(a, bt.logical, acc_f, 0.0, sred);
 }
 

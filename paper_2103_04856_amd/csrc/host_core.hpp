@@ -34,14 +34,16 @@ constexpr int kGraphPairs = 8;  // descent steps per captured graph: 2 x kGraphP
 template <typename T>
 using SweepFn = void (*)(fe::SweepArgs<T>);
 
+constexpr int kBodies = 4;   // fe::SweepBody values
+
 // The sweep kernels of one launch shape: [fe::SweepBody] for the gradient, the
 // plain step and the Adam step (the single-body ones only for the leading
 // shapes; nullptr where not built).
 template <typename T>
 struct Kernels {
-  SweepFn<T> grad[3] = {nullptr, nullptr, nullptr};
-  SweepFn<T> step[3] = {nullptr, nullptr, nullptr};
-  SweepFn<T> adam[3] = {nullptr, nullptr, nullptr};
+  SweepFn<T> grad[kBodies] = {};
+  SweepFn<T> step[kBodies] = {};
+  SweepFn<T> adam[kBodies] = {};
   SweepFn<T> energy = nullptr;
 };
 
@@ -52,8 +54,8 @@ struct Variant {
   Kernels<double> k64;
   Kernels<float> k32sp;    // with a coefficient field (only some variants have them)
   Kernels<double> k64sp;
-  SweepFn<float> k32box = nullptr;    // gradient with a box mask (padded, non-periodic fields)
-  SweepFn<double> k64box = nullptr;
+  std::array<SweepFn<float>, kBodies> k32box{};   // gradient with a box mask (padded, non-periodic fields)
+  std::array<SweepFn<double>, kBodies> k64box{};
   bool lead = false;   // a default candidate: chosen by the ring work its tiles cover a grid with
 };
 
@@ -70,17 +72,39 @@ Kernels<T> make_kernels() {
     k.grad[fe::kBodyFull] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, false, fe::kBodyFull>;
     k.step[fe::kBodyFull] = fe::grad_sweep<T, TX, TY, NT, fe::kStepGD, false, false, fe::kBodyFull>;
     k.adam[fe::kBodyFull] = fe::grad_sweep<T, TX, TY, NT, fe::kStepAdam, false, false, fe::kBodyFull>;
+    k.grad[fe::kBodyTrace] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, false, fe::kBodyTrace>;
+    k.step[fe::kBodyTrace] = fe::grad_sweep<T, TX, TY, NT, fe::kStepGD, false, false, fe::kBodyTrace>;
+    k.adam[fe::kBodyTrace] = fe::grad_sweep<T, TX, TY, NT, fe::kStepAdam, false, false, fe::kBodyTrace>;
   }
   k.energy = fe::energy_sweep<T, TX, TY, NT, SP>;
   return k;
 }
 
-// The kernel of `kind` (a fe::SweepMode) for a batch whose instances all take
-// `body`, or the per-instance one where no single-body kernel is built.
+// The gradient kernels of a box mask (padded, non-periodic fields) for a launch
+// shape, by body like Kernels.
+template <typename T, int TX, int TY, int NT, bool BODIES = false>
+std::array<SweepFn<T>, kBodies> make_box_kernels() {
+  std::array<SweepFn<T>, kBodies> k{};
+  k[fe::kBodyAny] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, true>;
+  if constexpr (BODIES) {
+    k[fe::kBodyNoS] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, true, fe::kBodyNoS>;
+    k[fe::kBodyFull] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, true, fe::kBodyFull>;
+    k[fe::kBodyTrace] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, true, fe::kBodyTrace>;
+  }
+  return k;
+}
+
+// The kernel for a batch whose instances all take `body`, or the per-instance
+// one where no single-body kernel is built.
+template <typename T>
+SweepFn<T> body_kernel(const SweepFn<T>* f, int body) {
+  return f[body] ? f[body] : f[fe::kBodyAny];
+}
+
+// The kernel of `kind` (a fe::SweepMode).
 template <typename T>
 SweepFn<T> sweep_kernel(const Kernels<T>& k, int kind, int body) {
-  const SweepFn<T>* f = kind == fe::kGrad ? k.grad : kind == fe::kStepGD ? k.step : k.adam;
-  return f[body] ? f[body] : f[fe::kBodyAny];
+  return body_kernel<T>(kind == fe::kGrad ? k.grad : kind == fe::kStepGD ? k.step : k.adam, body);
 }
 
 // Static LDS of grad_sweep is (4 (TX+4)(TY+4) + 7 (TX+2)(TY+2)) sizeof(T) plus
@@ -90,13 +114,13 @@ const std::vector<Variant>& variants() {
   static const std::vector<Variant> v = [] {
     std::vector<Variant> r;
     auto add32 = [&](int tx, int ty, int nt, Kernels<float> k, Kernels<float> ksp = {},
-                     SweepFn<float> kbox = nullptr) {
-      Variant x{tx, ty, nt, 1, k, {}, ksp, {}, kbox, nullptr};
+                     std::array<SweepFn<float>, kBodies> kbox = {}) {
+      Variant x{tx, ty, nt, 1, k, {}, ksp, {}, kbox, {}};
       r.push_back(x);
     };
     auto add64 = [&](int tx, int ty, int nt, Kernels<double> k, Kernels<double> ksp = {},
-                     SweepFn<double> kbox = nullptr) {
-      Variant x{tx, ty, nt, 2, {}, k, {}, ksp, nullptr, kbox};
+                     std::array<SweepFn<double>, kBodies> kbox = {}) {
+      Variant x{tx, ty, nt, 2, {}, k, {}, ksp, {}, kbox};
       r.push_back(x);
     };
     // the coefficient-field and box kernels exist for a few large tiles, one
@@ -111,30 +135,30 @@ const std::vector<Variant>& variants() {
     add32(32, 32, 512, make_kernels<float, 32, 32, 512, false, true>());
     r.back().lead = true;
     add32(50, 20, 512, make_kernels<float, 50, 20, 512, false, true>(), {},
-          fe::grad_sweep<float, 50, 20, 512, fe::kGrad, false, true>);
+          make_box_kernels<float, 50, 20, 512, true>());
     r.back().lead = true;
     add32(64, 16, 512, make_kernels<float, 64, 16, 512>(), make_kernels<float, 64, 16, 512, true>(),
-          fe::grad_sweep<float, 64, 16, 512, fe::kGrad, false, true>);
+          make_box_kernels<float, 64, 16, 512, true>());
     add32(64, 32, 1024, make_kernels<float, 64, 32, 1024>());
     add32(64, 32, 768, make_kernels<float, 64, 32, 768>());
     add32(64, 16, 1024, make_kernels<float, 64, 16, 1024>());
     add32(64, 8, 512, make_kernels<float, 64, 8, 512>());
     add32(32, 16, 512, make_kernels<float, 32, 16, 512>());
     add32(32, 8, 256, make_kernels<float, 32, 8, 256>(), make_kernels<float, 32, 8, 256, true>(),
-          fe::grad_sweep<float, 32, 8, 256, fe::kGrad, false, true>);
+          make_box_kernels<float, 32, 8, 256>());
     add32(16, 16, 256, make_kernels<float, 16, 16, 256>());
     add32(16, 8, 128, make_kernels<float, 16, 8, 128>());
     add32(8, 8, 64, make_kernels<float, 8, 8, 64>(), make_kernels<float, 8, 8, 64, true>(),
-          fe::grad_sweep<float, 8, 8, 64, fe::kGrad, false, true>);
+          make_box_kernels<float, 8, 8, 64>());
     add64(32, 16, 512, make_kernels<double, 32, 16, 512, false, true>(), make_kernels<double, 32, 16, 512, true>(),
-          fe::grad_sweep<double, 32, 16, 512, fe::kGrad, false, true>);
+          make_box_kernels<double, 32, 16, 512, true>());
     r.back().lead = true;
     add64(32, 8, 256, make_kernels<double, 32, 8, 256>());
     add64(16, 16, 256, make_kernels<double, 16, 16, 256>());
     add64(16, 8, 128, make_kernels<double, 16, 8, 128>(), make_kernels<double, 16, 8, 128, true>(),
-          fe::grad_sweep<double, 16, 8, 128, fe::kGrad, false, true>);
+          make_box_kernels<double, 16, 8, 128>());
     add64(8, 8, 64, make_kernels<double, 8, 8, 64>(), make_kernels<double, 8, 8, 64, true>(),
-          fe::grad_sweep<double, 8, 8, 64, fe::kGrad, false, true>);
+          make_box_kernels<double, 8, 8, 64>());
     return r;
   }();
   return v;
@@ -147,11 +171,11 @@ const Kernels<float>& kernels_of<float>(const Variant& v, bool sp) { return sp ?
 template <>
 const Kernels<double>& kernels_of<double>(const Variant& v, bool sp) { return sp ? v.k64sp : v.k64; }
 template <typename T>
-SweepFn<T> box_kernel_of(const Variant& v);
+SweepFn<T> box_kernel_of(const Variant& v, int body);
 template <>
-SweepFn<float> box_kernel_of<float>(const Variant& v) { return v.k32box; }
+SweepFn<float> box_kernel_of<float>(const Variant& v, int body) { return body_kernel<float>(v.k32box.data(), body); }
 template <>
-SweepFn<double> box_kernel_of<double>(const Variant& v) { return v.k64box; }
+SweepFn<double> box_kernel_of<double>(const Variant& v, int body) { return body_kernel<double>(v.k64box.data(), body); }
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -306,13 +330,19 @@ fe::GridConsts<T> grid_consts(double h) {
   return k;
 }
 
-// The body every instance of `p` takes (fe::has_s_terms on the typed constants,
-// as the kernels decide it), or kBodyAny if they differ.
+// The body every instance of `p` takes (fe::has_s_terms and fe::has_trace_only
+// on the typed constants, as the kernels decide it), or kBodyAny if some have S~
+// terms and others not. A batch without S~ terms takes the trace body only where
+// every instance can.
 template <typename T>
 int batch_body(const fe::InstParams<T>* p, int batch) {
-  int nos = 0;
-  for (int b = 0; b < batch; ++b) nos += (p[b].C3 == T(0) && p[b].C5 == T(0)) ? 1 : 0;
-  return nos == batch ? fe::kBodyNoS : nos == 0 ? fe::kBodyFull : fe::kBodyAny;
+  int nos = 0, trace = 0;
+  for (int b = 0; b < batch; ++b) {
+    const bool n = p[b].C3 == T(0) && p[b].C5 == T(0);
+    nos += n ? 1 : 0;
+    trace += n && p[b].C1 == T(0) ? 1 : 0;
+  }
+  return trace == batch ? fe::kBodyTrace : nos == batch ? fe::kBodyNoS : nos == 0 ? fe::kBodyFull : fe::kBodyAny;
 }
 
 int upload_params(fe_ctx* c) {
@@ -423,7 +453,7 @@ Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, i
 // fe::SweepMode) with `variant` on this context.
 template <typename T>
 SweepFn<T> sweep_fn(const fe_ctx* c, const Variant& v, int kind) {
-  if (c->use_box) return box_kernel_of<T>(v);
+  if (c->use_box) return box_kernel_of<T>(v, c->body);
   const Kernels<T>& k = kernels_of<T>(v, c->use_cfield);
   return kind < 0 ? k.energy : sweep_kernel<T>(k, kind, c->use_cfield ? (int)fe::kBodyAny : c->body);
 }
@@ -452,7 +482,7 @@ bool has_sp(int v, int dtype) {
 
 bool has_box(int v, int dtype) {
   const Variant& x = variants()[v];
-  return dtype == FE_F32 ? x.k32box != nullptr : x.k64box != nullptr;
+  return dtype == FE_F32 ? x.k32box[fe::kBodyAny] != nullptr : x.k64box[fe::kBodyAny] != nullptr;
 }
 
 // The variant a sweep launches: the chosen one, unless a coefficient field or
@@ -822,7 +852,7 @@ int tune_key(const fe_ctx* c, int kind, std::string& key) {
   for (char& ch : arch)
     if (ch == ' ') ch = '_';
   static const char* kinds[] = {"grad", "step", "adam"};
-  static const char* bodies[] = {"any", "nos", "full"};
+  static const char* bodies[] = {"any", "nos", "full", "trace"};
   char buf[320];
   std::snprintf(buf, sizeof(buf), "%dx%dx%dx%d:%s:%s:%s:%s:%s", c->grid.nx, c->grid.ny, c->grid.nz, c->grid.batch,
                 c->grid.dtype == FE_F32 ? "f32" : "f64", kinds[kind], bodies[c->body],
