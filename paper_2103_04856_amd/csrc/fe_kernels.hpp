@@ -56,25 +56,27 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void* base, u
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
 
-__device__ __forceinline__ void buffer_store(float v, __amdgpu_buffer_rsrc_t r, unsigned off) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, 0, 0);
+// `uniform`: a block-uniform addition to the offset, a scalar operand of the
+// instruction (not part of the range check: only stores that must land take one).
+__device__ __forceinline__ void buffer_store(float v, __amdgpu_buffer_rsrc_t r, unsigned off, unsigned uniform = 0) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, (int)uniform, 0);
 }
 
-__device__ __forceinline__ void buffer_store(double v, __amdgpu_buffer_rsrc_t r, unsigned off) {
+__device__ __forceinline__ void buffer_store(double v, __amdgpu_buffer_rsrc_t r, unsigned off, unsigned uniform = 0) {
   typedef unsigned u32x2 __attribute__((__vector_size__(2 * sizeof(unsigned))));
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, (int)uniform, 0);
 }
 
 // Loads and stores through such a buffer take the 32-bit lane offset as an
 // operand of the instruction, so the compiler neither widens it to a 64-bit
 // lane address nor needs it kept opaque, and the plane address stays in
 // scalar registers.
-__device__ __forceinline__ float buffer_load(__amdgpu_buffer_rsrc_t r, unsigned off, float) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+__device__ __forceinline__ float buffer_load(__amdgpu_buffer_rsrc_t r, unsigned off, float, unsigned uniform = 0) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)uniform, 0));
 }
 
-__device__ __forceinline__ double buffer_load(__amdgpu_buffer_rsrc_t r, unsigned off, double) {
-  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+__device__ __forceinline__ double buffer_load(__amdgpu_buffer_rsrc_t r, unsigned off, double, unsigned uniform = 0) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)uniform, 0));
 }
 
 // Issue priority of a sweep's waves at plane `it` of the n planes of its z
@@ -94,6 +96,17 @@ __device__ __forceinline__ void progress_priority(int it, int n) {
   if (it == n / 2) __builtin_amdgcn_s_setprio(2);
   if (it == (3 * n) / 4) __builtin_amdgcn_s_setprio(1);
   if (it == (9 * n) / 10) __builtin_amdgcn_s_setprio(0);
+}
+
+// A value that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ float uniform(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+
+__device__ __forceinline__ double uniform(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
 }
 
 __device__ __forceinline__ int wrap_index(int v, int n) {
@@ -140,7 +153,7 @@ __device__ __forceinline__ int xcd_logical_block(int linear, int total) {
 
 // What the fused sweep writes.
 enum SweepMode {
-  kGrad = 0,      // dst = dF_h/du (h^3 included); partial[1] = sum of src
+  kGrad = 0,      // dst = dF_h/du (h^3 included); partial[1] = 0
   kStepGD = 1,    // dst = u - tau dF_h/du, u = src + shift of src; partial[1] = sum of dst
   kStepAdam = 2,  // dst = u - lr mhat / (sqrt(vhat) + adam_eps), moments updated in place
 };
@@ -153,7 +166,7 @@ struct SweepArgs {
   const double* prev_partials;  // steps: the partials of the step that wrote src; the instance's shift
                                 // mass - mean(src) formed from them is added to src (null: no shift)
   double* partials;             // out: [batch][blocks_per_instance][2] per-block sums of the energy
-                                // density and of the field (steps: the stepped field, else src)
+                                // density and of the stepped field
   const double* mass;           // steps: [batch] target means
   double inv_nvox;
   T* m1;                        // Adam: first moment, same layout as src
@@ -195,6 +208,7 @@ __device__ __forceinline__ InstParams<T> with_coeffs(InstParams<T> p, const Voxe
   p.C4 = v.c[3];
   p.C5 = v.c[4];
   p.C6 = v.c[5];
+  set_multiples(p);
   return p;
 }
 
@@ -254,6 +268,22 @@ __device__ __forceinline__ Stencil19<T> load_stencil(const char* bc, const char*
   s.xpyp = at(bc, C + UX + 1); s.xpym = at(bc, C + 1 - UX); s.xmyp = at(bc, C + UX - 1); s.xmym = at(bc, 0);
   s.xpzp = at(bp, C + 1); s.xpzm = at(bm, C + 1); s.xmzp = at(bp, C - 1); s.xmzm = at(bm, C - 1);
   s.ypzp = at(bp, C + UX); s.ypzm = at(bm, C + UX); s.ymzp = at(bp, C - UX); s.ymzm = at(bm, C - UX);
+  return s;
+}
+
+// The stencil of the voxel one row above the one whose stencil is s0: ten of its
+// samples are s0's, nine are read. The pointers are s0's, as in load_stencil.
+template <typename T, int UX>
+__device__ __forceinline__ Stencil19<T> load_stencil_above(const Stencil19<T>& s0, const char* bc, const char* bm,
+                                                           const char* bp) {
+  auto at = [](const char* b, int i) { return *reinterpret_cast<const T*>(b + i * (int)sizeof(T)); };
+  constexpr int D = 2 * UX + 1;                // the centre
+  Stencil19<T> s;
+  s.c = s0.yp;
+  s.ym = s0.c; s.xm = s0.xmyp; s.xp = s0.xpyp; s.xmym = s0.xm; s.xpym = s0.xp;
+  s.yp = at(bc, D + UX); s.xmyp = at(bc, D + UX - 1); s.xpyp = at(bc, D + UX + 1);
+  s.zm = s0.ypzm; s.ymzm = s0.zm; s.ypzm = at(bm, D + UX); s.xmzm = at(bm, D - 1); s.xpzm = at(bm, D + 1);
+  s.zp = s0.ypzp; s.ymzp = s0.zp; s.ypzp = at(bp, D + UX); s.xmzp = at(bp, D - 1); s.xpzp = at(bp, D + 1);
   return s;
 }
 
@@ -335,39 +365,80 @@ __device__ __forceinline__ BlockTile block_tile(const SweepArgs<T>& a) {
 // BOX: only voxels inside [box_lo, box_hi) carry a density; the others (the
 // padding of a non-periodic field) have zero adjoints, and the gradient is
 // written at every voxel, padding included, for the caller to fold back.
+template <typename T, int NT, int MODE, bool SP>
+constexpr int sweep_min_waves() {
+  // two FP64 blocks of 512 threads share a compute unit with up to 128 registers;
+  // the gradient sweeps with the S~ terms would take 129 or 130
+  return sizeof(T) == 8 && NT == 512 && MODE == kGrad && !SP ? 4 : 1;
+}
+
 template <typename T, int TX, int TY, int NT, int MODE, bool SP = false, bool BOX = false, int BODY = kBodyAny>
-__global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
+__global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad_sweep(SweepArgs<T> a) {
   constexpr int UX = TX + 4, UY = TY + 4;      // u window: interior + halo 2
   constexpr int RX = TX + 2, RY = TY + 2;      // adjoint ring: interior + 1
   constexpr int NU = (UX * UY + NT - 1) / NT;  // u elements staged per thread per plane
   constexpr int NI = TX * TY;                  // interior (output) voxels
   constexpr int NO = (NI + NT - 1) / NT;       // interior voxels per thread
-  constexpr int NB = 2 * RX + 2 * TY;          // border voxels of the ring
-  constexpr int NW = (NI + NB + NT - 1) / NT;  // ring voxels per thread (interior first)
-  // The gather reads a_x's and b_xx's adjoints at the same two neighbours
-  // (x +- 1), and a_y's and b_yy's at y +- 1: without a coefficient field each
-  // such pair is one 8-byte record (XP, YP: two field rows of sx seen as
-  // RY * RX records), written with one instruction and read with one paired
-  // instruction per neighbour pair; with one (whose kernels have no registers
-  // to spare for the wider reads) the four are rows of their own, in the same
-  // storage. BXY, BXZ and BYZ are single fields; kBodyTrace has none of them.
-  enum { XP = 0, YP = 2, BXY = 4, BXZ, BYZ, ALL_FIELDS };
   constexpr bool kMixed = BODY != kBodyTrace;  // the body has mixed differences
+  // COLS: a thread's two output voxels (NO = 2) are two rows of one column, whose
+  // stencils share samples: 28 LDS reads for both instead of 38. Otherwise they are
+  // NT voxels apart, which the steps of the bodies with mixed differences keep:
+  // their FP32 sums of the stepped field pair these voxels, and their trajectories
+  // hang on the last bit of the mass shift (see SUMS below).
+  // The ring's border follows the interior: with COLS in a list of its own, else
+  // from the same index space. The waves without an item skip the last turn, so
+  // its length is kept to as few waves as possible:
+  //   * COLS: threads without output voxels (50 x 20: 12 of 512) take pairs of
+  //     voxels of the side columns along with the others' output pairs;
+  //   * the corners, which only BXY is read from, are among the items only where
+  //     the last wave has lanes to spare; else four threads of the next wave form
+  //     that one value (32 x 32: the other 128 are two waves, where 132 took a
+  //     third one); kBodyTrace needs none.
+  constexpr bool COLS = NO == 2 && TY % 2 == 0 && (MODE == kGrad || !kMixed);
+  constexpr int kIdlePairs = COLS ? (NT - NI / 2 < TY ? NT - NI / 2 : TY) : 0;
+  constexpr int kEdges = 2 * TX + 2 * (TY - kIdlePairs);     // border voxels listed, corners aside
+  constexpr int kTurns = (COLS ? 2 * NT : NI) + kEdges;      // thread turns up to the last listed edge
+  constexpr bool kCornersListed = kMixed && kTurns % kWave != 0 && kTurns % kWave + 4 <= kWave;
+  constexpr int kList = kEdges + (kCornersListed ? 4 : 0);
+  constexpr bool kCornerPass = kMixed && !kCornersListed;
+  constexpr int kCornerTid = (kTurns + kWave - 1) / kWave * kWave % NT;   // the threads of corners not listed
+  static_assert(TY % 2 == 0 && (!COLS || kList <= NT), "side columns in pairs, one border voxel per thread");
+  constexpr int NW = COLS ? 3 : (NI + kList + NT - 1) / NT;  // ring voxels per thread, interior first
+  // What the gather reads of its x and y neighbours, in four field rows:
+  //   * SUMS: the a_x and b_xx adjoints only as b_xx + a_x (row 0, read at x + 1)
+  //     and b_xx - a_x (row 1, read at x - 1), formed once per ring voxel, and
+  //     those of y likewise in rows 2 and 3: one value per neighbour;
+  //   * otherwise the records (a_x / 2, b_xx) and (a_y / 2, b_yy), seen as RY * RX
+  //     records of two rows each (with a coefficient field, whose kernels have no
+  //     registers to spare for the wider reads, rows of their own).
+  // SUMS moves 12 instead of 16 values per output voxel through the gather and
+  // takes fewer registers (128^3 FP64 sweep with the S~ terms: 128 instead of 139
+  // VGPRs, two blocks per compute unit instead of one, 41.6 -> 35 us). The other
+  // kernels keep the records and with them the order of their sums, bit for bit:
+  // what a loop iterates through them, plain steps and Algorithm 1 without S~
+  // terms above all, amplifies a rounding where |a| nearly vanishes (40 steps grow
+  // it from 1e-7 to 1e-2 at single voxels), for a gain of 2 %.
+  // BXY, BXZ and BYZ are read on both sides; kBodyTrace has none of them.
+  constexpr bool SUMS = BODY == kBodyTrace || (MODE == kGrad && BODY != kBodyNoS);
+  enum { XP = 0, YP = 2, BXY = 4, BXZ, BYZ, ALL_FIELDS };
   constexpr int NFIELD = kMixed ? ALL_FIELDS : BXY;
-  constexpr bool kPairs = !SP;
+  constexpr bool kPairs = !SUMS && !SP;
   constexpr bool STEP = MODE != kGrad;
 
   __shared__ T su[3][UY * UX];
   __shared__ alignas(4 * sizeof(T)) T sx[NFIELD][RY * RX];
-  FieldPair<T>* const xrec = reinterpret_cast<FieldPair<T>*>(&sx[XP][0]);   // (a_x / 2, b_xx) adjoints
-  FieldPair<T>* const yrec = reinterpret_cast<FieldPair<T>*>(&sx[YP][0]);   // (a_y / 2, b_yy) adjoints
-  auto put_xy = [&](int v, T gx, T bxx, T gy, T byy) {
-    if constexpr (kPairs) {
-      xrec[v] = FieldPair<T>{gx, bxx};
-      yrec[v] = FieldPair<T>{gy, byy};
+  FieldPair<T>* const xrec = reinterpret_cast<FieldPair<T>*>(&sx[XP][0]);
+  FieldPair<T>* const yrec = reinterpret_cast<FieldPair<T>*>(&sx[YP][0]);
+  auto put_xy = [&](int v, T hgx, T bxx, T hgy, T byy) {
+    if constexpr (SUMS) {
+      sx[XP][v] = bxx + T(2) * hgx; sx[XP + 1][v] = bxx - T(2) * hgx;
+      sx[YP][v] = byy + T(2) * hgy; sx[YP + 1][v] = byy - T(2) * hgy;
+    } else if constexpr (kPairs) {
+      xrec[v] = FieldPair<T>{hgx, bxx};
+      yrec[v] = FieldPair<T>{hgy, byy};
     } else {
-      sx[XP][v] = gx; sx[XP + 1][v] = bxx;
-      sx[YP][v] = gy; sx[YP + 1][v] = byy;
+      sx[XP][v] = hgx; sx[XP + 1][v] = bxx;
+      sx[YP][v] = hgy; sx[YP + 1][v] = byy;
     }
   };
   auto put_mixed = [&](int v, T bxy, T bxz, T byz) {
@@ -406,15 +477,25 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
                   ? (unsigned)(wrap_index(y0 - 2 + ey, a.ny) * a.nx + wrap_index(x0 - 2 + ex, a.nx)) * sizeof(T)
                   : 0u;
   }
-  unsigned ooff[NO];
+  // this thread's output voxel j: whether it has one, its tile column and row, its ring position
+  auto has_out = [&](int j) { return COLS ? tid < NI / 2 : tid + j * NT < NI; };
+  auto out_x = [&](int j) { return COLS ? tid % TX : (tid + j * NT) % TX; };
+  auto out_y = [&](int j) { return COLS ? 2 * (tid / TX) + j : (tid + j * NT) / TX; };
+  auto out_pos = [&](int j) { return has_out(j) ? (out_y(j) + 1) * RX + out_x(j) + 1 : RX + 1; };
+  // with COLS the second voxel is one row on from the first: it takes the first
+  // one's addresses, plus a row in scalar registers or immediates
+  constexpr int NA = COLS ? 1 : NO;            // output voxels with addresses of their own
+  unsigned ooff[NA];
   bool oin[NO];                                // an output voxel inside the grid
 #pragma unroll
   for (int j = 0; j < NO; ++j) {
-    const int w = tid + j * NT;
-    const int gx = x0 + w % TX, gy = y0 + w / TX;
-    oin[j] = w < TX * TY && gx < a.nx && gy < a.ny;
-    ooff[j] = oin[j] ? (unsigned)(gy * a.nx + gx) * sizeof(T) : 0u;
+    const int gx = x0 + out_x(j), gy = y0 + out_y(j);
+    oin[j] = has_out(j) && gx < a.nx && gy < a.ny;
+    if (j < NA) ooff[j] = oin[j] ? (unsigned)(gy * a.nx + gx) * sizeof(T) : 0u;
   }
+  const unsigned row_bytes = COLS ? (unsigned)a.nx * sizeof(T) : 0u;
+  auto off_of = [&](int j) { return ooff[COLS ? 0 : j]; };            // lane offset and
+  auto row_of = [&](int j) { return COLS && j ? row_bytes : 0u; };    // uniform part of output voxel j
   T pre[NU];
   T shift = T(0);                              // steps: the uniform shift of src, set below
   const unsigned pbytes = (unsigned)(plane * sizeof(T));
@@ -429,82 +510,103 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
 #pragma unroll
     for (int j = 0; j < NU; ++j) {
       const int e = tid + j * NT;
-      if (e < UX * UY) su[slot][e] = pre[j] + shift;
+      if (e < UX * UY) su[slot][e] = STEP ? pre[j] + shift : pre[j];
     }
   };
-  // ring position of border voxel b (top row, bottom row, then the two side columns)
-  auto border_pos = [](int b) {
-    if (b < RX) return b;
-    if (b < 2 * RX) return (RY - 1) * RX + (b - RX);
-    const int k = b - 2 * RX;
-    return (1 + (k >> 1)) * RX + ((k & 1) ? RX - 1 : 0);
+  // this thread's ring item j (interior first, then the border): whether it has
+  // one, its ring position; item kCornerItem is the corner of a thread of
+  // kCornerPass (the last item, which those threads do not have, or one more)
+  constexpr int kCornerItem = kCornerTid > 0 ? NW - 1 : NW;
+  constexpr int NS = kCornerPass && kCornerItem == NW ? NW + 1 : NW;
+  const bool corner_turn = kCornerPass && tid >= kCornerTid && tid < kCornerTid + 4;
+  auto has_item = [&](int j) {
+    if (COLS) return j < 2 ? tid < NI / 2 + kIdlePairs : tid < kList;
+    return tid + j * NT < NI + kList;
   };
-  // ring position of this thread's ring item j (interior first, then the border)
-  auto ring_pos = [&](int j) {
-    const int item = tid + j * NT;
-    return item < NI ? (item / TX + 1) * RX + item % TX + 1 : border_pos(item - NI);
+  auto is_out = [&](int j) { return j < NO && has_out(j); };
+  auto ring_item = [&](int j) {
+    if (is_out(j)) return (out_y(j) + 1) * RX + out_x(j) + 1;
+    auto corner = [](int k) { return (k & 2 ? (RY - 1) * RX : 0) + (k & 1 ? RX - 1 : 0); };
+    if (kCornerPass && j == kCornerItem && corner_turn) return corner(tid - kCornerTid);
+    // side pair q: rows 2 q', 2 q' + 1 of the left (q < TY / 2) or right column
+    auto side = [](int q) { return (1 + 2 * (q % (TY / 2))) * RX + (q < TY / 2 ? 0 : RX - 1); };
+    if (j >= NW || !has_item(j)) return RX + 1;
+    if (COLS && j < 2) return side(TY - 1 - (tid - NI / 2));
+    const int b = COLS ? tid : tid + j * NT - NI;            // bottom row, top row, sides, corners
+    if (b < 2 * TX) return (b < TX ? 0 : (RY - 1) * RX) + b % TX + 1;
+    if (b < kEdges) return side((b - 2 * TX) / 2) + (b - 2 * TX) % 2 * RX;
+    return corner(b - kEdges);
   };
+  auto ring_pos = [&](int j) { return COLS && j == 1 ? ring_item(0) + RX : ring_item(j); };
   // LDS byte offset of each ring item's stencil base (its (x-1, y-1) sample) in a
   // u window plane, the same in every plane
-  unsigned slo[NW];
+  unsigned slo[NS];
 #pragma unroll
-  for (int j = 0; j < NW; ++j) {
+  for (int j = 0; j < NS; ++j) {
     const int v = ring_pos(j);
-    slo[j] = stencil_base<T, UX>((v / RX + 1) * UX + v % RX + 1);
+    slo[j] = COLS && j == 1 ? slo[0] + UX * (unsigned)sizeof(T)
+                            : stencil_base<T, UX>((v / RX + 1) * UX + v % RX + 1);
   }
   // SP: in-plane offsets of this thread's ring voxels and their coefficients
   const size_t vol = plane * a.nz;
   const VoxelCoeffs<T>* cfb = SP ? coeff_records(a.cfield) + (size_t)bt.inst * vol : nullptr;
-  unsigned coff[SP ? NW : 1];                  // byte offsets within a plane of records
-  VoxelCoeffs<T> cv[SP ? NW : 1];
+  unsigned coff[SP ? NS : 1];                  // byte offsets within a plane of records
+  VoxelCoeffs<T> cv[SP ? NS : 1];
   if (SP) {
 #pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      const int item = tid + j * NT;
-      int v = 0;
-      if (item < NI) v = (item / TX + 1) * RX + item % TX + 1;
-      else if (item < NI + NB) v = border_pos(item - NI);
+    for (int j = 0; j < NS; ++j) {
+      const int v = ring_pos(j);
       coff[j] = (unsigned)(wrap_index(y0 - 1 + v / RX, a.ny) * a.nx + wrap_index(x0 - 1 + v % RX, a.nx)) *
                 (unsigned)sizeof(VoxelCoeffs<T>);
     }
   }
 
   double acc_f = 0.0, acc_m = 0.0;
-  // The gather reads seven fields around each output voxel, 4.6 KB apart in LDS
-  // (beyond the reach of a paired read's immediates), so every field needs an
-  // address of its own: with FP32 these are formed once here instead of at
-  // every plane (14 registers, which the FP32 kernels without a coefficient
-  // field have to spare at two blocks per compute unit).
-  constexpr bool kGatherBases = sizeof(T) == 4 && !SP;
+  // LDS addresses of the gather, formed once per block instead of at every plane
+  // (kernels without a coefficient field, which have the registers to spare). The
+  // rows are 4.6 KB apart in FP32, beyond the reach of a paired read's immediates:
+  // BXY, BXZ, BYZ and the two records, read in pairs, have an address each; the
+  // four rows of SUMS are single reads at immediate offsets from one address.
+  constexpr bool kGatherBases = !SP && (SUMS || sizeof(T) == 4);
   constexpr int NSINGLE = NFIELD - BXY;
-  lds_cptr<T> gbase[kGatherBases ? NO : 1][NSINGLE > 0 ? NSINGLE : 1];
-  lds_cptr<FieldPair<T>> gxr[kGatherBases ? NO : 1], gyr[kGatherBases ? NO : 1];
+  lds_cptr<T> gbase[kGatherBases ? NA : 1][NSINGLE > 0 ? NSINGLE : 1];
+  lds_cptr<T> gsum[kGatherBases ? NA : 1];
+  lds_cptr<FieldPair<T>> gxr[kGatherBases ? NA : 1], gyr[kGatherBases ? NA : 1];
   if constexpr (kGatherBases) {
 #pragma unroll
-    for (int j = 0; j < NO; ++j) {
-      const int w = tid + j * NT;
-      const int v = w < NI ? (w / TX + 1) * RX + w % TX + 1 : RX + 1;
+    for (int j = 0; j < NA; ++j) {
+      const int v = out_pos(j);
 #pragma unroll
       for (int f = 0; f < NSINGLE; ++f) gbase[j][f] = opaque_lds(&sx[BXY + f][v - RX - 1]);
-      gxr[j] = opaque_lds(&xrec[v - RX - 1]);
-      gyr[j] = opaque_lds(&yrec[v - RX - 1]);
+      if constexpr (SUMS) {
+        gsum[j] = opaque_lds(&sx[XP][v - RX - 1]);
+      } else {
+        gxr[j] = opaque_lds(&xrec[v - RX - 1]);
+        gyr[j] = opaque_lds(&yrec[v - RX - 1]);
+      }
     }
   }
-  // single field f (BXY, BXZ or BYZ) of the ring at index v + d, and the x and
-  // y records there, for this thread's output voxel j at v
-  auto sxat = [&](int j, int v, int f, int d) -> T {
-    if constexpr (kGatherBases) return gbase[j][f - BXY][d + RX + 1];
-    else return sx[f][v + d];
+  // field f (BXY, BXZ or BYZ) of the ring displaced by d from this thread's output
+  // voxel j; the x and y neighbours' rows of SUMS or their records there
+  auto sxat = [&](int j, int f, int d) -> T {
+    if constexpr (kGatherBases) return gbase[COLS ? 0 : j][f - BXY][d + RX + 1 + (COLS ? j * RX : 0)];
+    else return sx[f][out_pos(j) + d];
   };
-  auto xat = [&](int j, int v, int d) -> FieldPair<T> {
-    if constexpr (kGatherBases) return FieldPair<T>{gxr[j][d + RX + 1].a, gxr[j][d + RX + 1].b};
-    else if constexpr (kPairs) return xrec[v + d];
-    else return FieldPair<T>{sx[XP][v + d], sx[XP + 1][v + d]};
+  auto sumat = [&](int j, int row, int d) -> T {
+    if constexpr (kGatherBases) return gsum[COLS ? 0 : j][row * (RY * RX) + d + RX + 1 + (COLS ? j * RX : 0)];
+    else return sx[row][out_pos(j) + d];
   };
-  auto yat = [&](int j, int v, int d) -> FieldPair<T> {
-    if constexpr (kGatherBases) return FieldPair<T>{gyr[j][d + RX + 1].a, gyr[j][d + RX + 1].b};
-    else if constexpr (kPairs) return yrec[v + d];
-    else return FieldPair<T>{sx[YP][v + d], sx[YP + 1][v + d]};
+  auto xat = [&](int j, int d) -> FieldPair<T> {
+    const int at = d + RX + 1 + (COLS ? j * RX : 0), b = COLS ? 0 : j;
+    if constexpr (kGatherBases) return FieldPair<T>{gxr[b][at].a, gxr[b][at].b};
+    else if constexpr (kPairs) return xrec[out_pos(j) + d];
+    else return FieldPair<T>{sx[XP][out_pos(j) + d], sx[XP + 1][out_pos(j) + d]};
+  };
+  auto yat = [&](int j, int d) -> FieldPair<T> {
+    const int at = d + RX + 1 + (COLS ? j * RX : 0), b = COLS ? 0 : j;
+    if constexpr (kGatherBases) return FieldPair<T>{gyr[b][at].a, gyr[b][at].b};
+    else if constexpr (kPairs) return yrec[out_pos(j) + d];
+    else return FieldPair<T>{sx[YP][out_pos(j) + d], sx[YP + 1][out_pos(j) + d]};
   };
   T c_prev[NO], l_prev[NO], l_pp[NO];
   T u_out[NO];                                 // u at this thread's output voxels of plane p-1
@@ -522,7 +624,7 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
     if (tid == 0) s_shift = a.prev_partials ? a.mass[bt.inst] - sm * a.inv_nvox : 0.0;
   }
   __syncthreads();
-  if (STEP) shift = T(s_shift);
+  if (STEP) shift = uniform(T(s_shift));
   stage(0);
   fetch(k0 - 1);
   stage(1);
@@ -552,16 +654,16 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
         const auto r1 = plane_rsrc(a.m1 + po, pbytes), r2 = plane_rsrc(a.m2 + po, pbytes);
 #pragma unroll
         for (int j = 0; j < NO; ++j) {
-          m1n[j] = oin[j] ? buffer_load(r1, ooff[j], T()) : T(0);
-          m2n[j] = oin[j] ? buffer_load(r2, ooff[j], T()) : T(0);
+          m1n[j] = oin[j] ? buffer_load(r1, off_of(j), T(), row_of(j)) : T(0);
+          m2n[j] = oin[j] ? buffer_load(r2, off_of(j), T(), row_of(j)) : T(0);
         }
       }
     }
     if (SP) {
       const size_t zoff = (size_t)wrap_index(p, a.nz) * plane;
 #pragma unroll
-      for (int j = 0; j < NW; ++j)
-        if (tid + j * NT < NI + NB) {
+      for (int j = 0; j < NS; ++j)
+        if ((j < NW && has_item(j)) || (j == kCornerItem && corner_turn)) {
           // the coefficient records of plane p: a uniform plane address, one lane offset
           const char* cp = reinterpret_cast<const char*>(cfb + zoff);
           cv[j] = *reinterpret_cast<const VoxelCoeffs<T>*>(cp + lane_offset(coff[j]));
@@ -573,58 +675,68 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
     const bool out_plane = (p >= k0) && (p < kend);
     const int pz = BOX ? wrap_index(p, a.nz) : 0;
     const bool zin = !BOX || (pz >= a.box_lo[2] && pz < a.box_hi[2]);
-    auto eval = [&](int v, unsigned lo, VoxelAdjoint<T>& ad, const InstParams<T>& pv) {
+    const char* pc = reinterpret_cast<const char*>(su[sc]);
+    const char* pm = reinterpret_cast<const char*>(su[sm]);
+    const char* pp = reinterpret_cast<const char*>(su[sp]);
+    // the density of ring item j and its adjoint from the stencil st
+    auto adjoint = [&](int j, const Stencil19<T>& st, VoxelAdjoint<T>& ad) -> T {
       if (BOX) {
+        const int v = ring_pos(j);
         const int gx = wrap_index(x0 - 1 + v % RX, a.nx), gy = wrap_index(y0 - 1 + v / RX, a.ny);
         if (!zin || gx < a.box_lo[0] || gx >= a.box_hi[0] || gy < a.box_lo[1] || gy >= a.box_hi[1]) {
           ad = VoxelAdjoint<T>{};
-          put_xy(v, T(0), T(0), T(0), T(0));
-          put_mixed(v, T(0), T(0), T(0));
           return T(0);
         }
       }
-      const char* pc = reinterpret_cast<const char*>(su[sc]) + lo;
-      const char* pm = reinterpret_cast<const char*>(su[sm]) + lo;
-      const char* pp = reinterpret_cast<const char*>(su[sp]) + lo;
-      // with both bodies, the one without S~ terms where the instance has none,
-      // so an instance takes the same arithmetic in every batch it is part of
+      const InstParams<T> pv = SP ? with_coeffs(prm, cv[SP ? j : 0]) : prm;
+      auto reload = [&]() { return load_stencil<T, UX>(pc + slo[j], pm + slo[j], pp + slo[j]); };
+      // with both bodies, the one without S~ terms where the instance has none
       // (a coefficient field varies per voxel: always the full body)
-      auto st = [&]() { return load_stencil<T, UX>(pc, pm, pp); };
-      T f;
       if constexpr (BODY != kBodyAny)
-        f = voxel_density_adjoint_body<BODY>(st(), st, pv, a.k, ad);
+        return voxel_density_adjoint_body<BODY>(st, reload, pv, a.k, ad);
       else
-        f = voxel_density_adjoint<SP>(st(), st, pv, a.k, ad);
-      put_xy(v, ad.hgx, ad.nbxx, ad.hgy, ad.nbyy);
-      put_mixed(v, ad.dbxy, ad.dbxz, ad.dbyz);
-      return f;
+        return voxel_density_adjoint<SP>(st, reload, pv, a.k, ad);
     };
-    // Interior and border voxels are dealt out from one index space, so the
-    // per-thread counts differ by at most one (the border goes to the threads
-    // whose interior share is shorter).
     // the centre-only adjoint terms of this thread's output voxels: ub + 2 (b_zz +
     // b_xx + b_yy), a_z and b_zz (the last two also reach the planes above and below)
     T own_c0[NO], own_gz[NO], own_bzz[NO];
     T fpl = T(0);                              // this thread's energy of plane p (one FP64 add per plane)
+    auto eval = [&](int j, const Stencil19<T>& st) {
+      VoxelAdjoint<T> ad;
+      const T f = adjoint(j, st, ad);
+      const int v = ring_pos(j);
+      put_xy(v, ad.hgx, ad.nbxx, ad.hgy, ad.nbyy);
+      put_mixed(v, ad.dbxy, ad.dbxz, ad.dbyz);
+      if (j < NO) {
+        const int o = j < NO ? j : 0;
+        own_c0[o] = ad.ub + T(2) * ((ad.nbzz + ad.nbxx) + ad.nbyy);
+        own_gz[o] = ad.gz;
+        own_bzz[o] = ad.nbzz;
+        // u of output plane p-1 at this voxel, read before the second barrier (its
+        // slot takes plane p+2 in the next iteration)
+        if (STEP) u_out[o] = st.zm;
+        if (out_plane && oin[o]) fpl += f;
+      }
+    };
+    if constexpr (COLS) {
+      if (has_item(0)) {
+        const Stencil19<T> s0 = load_stencil<T, UX>(pc + slo[0], pm + slo[0], pp + slo[0]);
+        eval(0, s0);
+        // one voxel after the other: interleaved, they take more registers
+        __asm__ volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        eval(1, load_stencil_above<T, UX>(s0, pc + slo[0], pm + slo[0], pp + slo[0]));
+      }
+    }
 #pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      const int item = tid + j * NT;
-      if (item < NI + NB) {
-        const bool inner = item < NI;
-        const int ix = item % TX, iy = item / TX;
+    for (int j = COLS ? 2 : 0; j < NW; ++j)
+      if (has_item(j)) eval(j, load_stencil<T, UX>(pc + slo[j], pm + slo[j], pp + slo[j]));
+    if constexpr (kCornerPass) {
+      if (corner_turn) {
         VoxelAdjoint<T> ad;
-        const T f = eval(ring_pos(j), slo[j], ad, SP ? with_coeffs(prm, cv[j]) : prm);
-        if (j < NO && inner) {
-          own_c0[j] = ad.ub + T(2) * ((ad.nbzz + ad.nbxx) + ad.nbyy);
-          own_gz[j] = ad.gz;
-          own_bzz[j] = ad.nbzz;
-          // u of output plane p-1 at this voxel (the stencil's centre in plane
-          // p-1), read before the second barrier (its slot takes plane p+2 in
-          // the next iteration)
-          u_out[j] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(su[sm]) + slo[j] +
-                                                 (UX + 1) * sizeof(T));
-          if (out_plane && x0 + ix < a.nx && y0 + iy < a.ny) fpl += f;
-        }
+        const unsigned lo = slo[kCornerItem];
+        adjoint(kCornerItem, load_stencil<T, UX>(pc + lo, pm + lo, pp + lo), ad);
+        sx[BXY][ring_pos(kCornerItem)] = ad.dbxy;
       }
     }
     acc_f += double(fpl);
@@ -632,8 +744,8 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
 
     // ---- transposed stencils on the interior ----
     // The b adjoints are held negated (nb = -df/db), which flips their signs
-    // here; the records' first values hold half the a_x, a_y derivatives and BXY, BXZ, BYZ twice
-    // the (negated) b_ab ones, hence the factors 2 and 1/2.
+    // here; the records' first values hold half the a_x, a_y derivatives and BXY,
+    // BXZ, BYZ twice the (negated) b_ab ones, hence the factors 2 and 1/2.
     T mpl = T(0);                              // this thread's sum of the field written for plane p - 1
     const size_t po = (size_t)(it >= 2 ? p - 1 : 0) * plane;   // output plane p - 1 (written from it = 2)
     const auto rd = plane_rsrc(dstb + po, pbytes);
@@ -641,50 +753,49 @@ __global__ __launch_bounds__(NT) void grad_sweep(SweepArgs<T> a) {
     const auto rm2 = plane_rsrc(MODE == kStepAdam ? a.m2 + inst_off + po : dstb, pbytes);
 #pragma unroll
     for (int j = 0; j < NO; ++j) {
-      const int w = tid + j * NT;
-      if (w < TX * TY) {
-        const int ix = w % TX, iy = w / TX;
-        const int v = (iy + 1) * RX + ix + 1;
+      if (has_out(j)) {
         const T bzz = own_bzz[j];
         T gd = own_gz[j];
         if constexpr (kMixed)
-          gd += T(0.5) * ((sxat(j, v, BXZ, 1) - sxat(j, v, BXZ, -1)) +
-                          (sxat(j, v, BYZ, RX) - sxat(j, v, BYZ, -RX)));
+          gd += T(0.5) * ((sxat(j, BXZ, 1) - sxat(j, BXZ, -1)) + (sxat(j, BYZ, RX) - sxat(j, BYZ, -RX)));
         const T upn = gd + bzz;        // minus what plane p adds to output plane p-1
         const T lo = gd - bzz;         // what plane p adds to output plane p+1
         if (it >= 2 && oin[j]) {
           const T g = (c_prev[j] - upn) + l_pp[j];
-          const unsigned o = ooff[j];
-          const T uc = u_out[j];
+          const unsigned o = off_of(j), orow = row_of(j);
+          const T uc = STEP ? u_out[j] : T(0);
           if (MODE == kStepGD) {
             const T un = uc - a.tau * g;
-            buffer_store(un, rd, o);
+            buffer_store(un, rd, o, orow);
             mpl += un;
           } else if (MODE == kStepAdam) {
             const T mo = a.beta1 * m1c[j] + (T(1) - a.beta1) * g;
             const T vo = a.beta2 * m2c[j] + (T(1) - a.beta2) * g * g;
-            buffer_store(mo, rm1, o);
-            buffer_store(vo, rm2, o);
+            buffer_store(mo, rm1, o, orow);
+            buffer_store(vo, rm2, o, orow);
             const T un = uc - a.tau * (mo * bc1) * rcp_t(sqrt_t(vo * bc2) + a.adam_eps);
-            buffer_store(un, rd, o);
+            buffer_store(un, rd, o, orow);
             mpl += un;
           } else {
-            buffer_store(g, rd, o);
-            mpl += uc;
+            buffer_store(g, rd, o, orow);
           }
         }
-        const FieldPair<T> xp1 = xat(j, v, 1), xm1 = xat(j, v, -1);
-        const FieldPair<T> yp1 = yat(j, v, RX), ym1 = yat(j, v, -RX);
-        T cin = own_c0[j]
+        T cin;
+        if constexpr (SUMS) {
+          cin = own_c0[j] - ((sumat(j, XP, 1) + sumat(j, XP + 1, -1)) + (sumat(j, YP, RX) + sumat(j, YP + 1, -RX)));
+        } else {
+          const FieldPair<T> xp1 = xat(j, 1), xm1 = xat(j, -1);
+          const FieldPair<T> yp1 = yat(j, RX), ym1 = yat(j, -RX);
+          cin = own_c0[j]
                 - T(2) * ((xp1.a - xm1.a) + (yp1.a - ym1.a))
                 - ((xp1.b + xm1.b) + (yp1.b + ym1.b));
+        }
         if constexpr (kMixed)
-          cin -= T(0.5) * ((sxat(j, v, BXY, RX + 1) - sxat(j, v, BXY, -RX + 1)) -
-                           (sxat(j, v, BXY, RX - 1) - sxat(j, v, BXY, -RX - 1)));
+          cin -= T(0.5) * ((sxat(j, BXY, RX + 1) - sxat(j, BXY, -RX + 1)) -
+                           (sxat(j, BXY, RX - 1) - sxat(j, BXY, -RX - 1)));
         l_pp[j] = l_prev[j];
         l_prev[j] = lo;
         c_prev[j] = cin;
-
       }
     }
     acc_m += double(mpl);
@@ -991,6 +1102,7 @@ __global__ __launch_bounds__(64) void scale_params(const InstParams<T>* __restri
     q.C5 = T(double(q.C5) * f);
     q.C6 = T(double(q.C6) * f);
     q.Co = T(double(q.Co) * f);
+    set_multiples(q);
     dst[b] = q;
   }
 }

@@ -45,9 +45,20 @@ struct InstParams {
   T lam;                       // h^2 / eps^2
   T C1, C2, C3, C4, C5, C6;    // h^3 c1 s^2, h^3 c2 s^2, h^3 c3 s^2, h^3 c4 s/(2h), h^3 c5 s/(2h), h^3 c6 eps/(4h^2)
   T xi, inv_xi;                // softplus width in X~ units: xi h^4 / eps^2, and its inverse
+  T C1x2, hC1, hC4, hC5;       // 2 C1, C1 / 2, C4 / 2, C5 / 2
   T Co;                        // orientation term of Sec. 5.2: h^3 eps mu / (4h^2) (0: off)
   T thx, thy, thz;             // its direction theta
 };
+
+// The multiples of the coefficients that the adjoint takes, kept in the table so
+// that a kernel holds them in scalar registers.
+template <typename T>
+__host__ __device__ inline void set_multiples(InstParams<T>& p) {
+  p.C1x2 = T(2) * p.C1;
+  p.hC1 = T(0.5) * p.C1;
+  p.hC4 = T(0.5) * p.C4;
+  p.hC5 = T(0.5) * p.C5;
+}
 
 // Grid constants shared by all instances.
 template <typename T>
@@ -256,10 +267,10 @@ __device__ __forceinline__ Forward<float> forward_fp32(const Stencil19<float>& s
   o.ax = s.xp - s.xm;
   o.ay = s.yp - s.ym;
   o.az = s.zp - s.zm;
-  const float c2u = c + c;
-  const float bxx = (s.xp + s.xm) - c2u;
-  const float byy = (s.yp + s.ym) - c2u;
-  const float bzz = (s.zp + s.zm) - c2u;
+  // 2 c is exact, so the multiply-add rounds as the difference does
+  const float bxx = __builtin_fmaf(-2.0f, c, s.xp + s.xm);
+  const float byy = __builtin_fmaf(-2.0f, c, s.yp + s.ym);
+  const float bzz = __builtin_fmaf(-2.0f, c, s.zp + s.zm);
   const float bxy = (s.xpyp - s.xpym) - (s.xmyp - s.xmym);
   const float bxz = (s.xpzp - s.xpzm) - (s.xmzp - s.xmzm);
   const float byz = (s.ypzp - s.ypzm) - (s.ymzp - s.ymzm);
@@ -381,8 +392,7 @@ __device__ __forceinline__ TraceForward<T> trace_forward(const Stencil19<T>& s, 
   o.ax = s.xp - s.xm;
   o.ay = s.yp - s.ym;
   o.az = s.zp - s.zm;
-  const T c2u = c + c;
-  const T lap = (((s.xp + s.xm) - c2u) + ((s.yp + s.ym) - c2u)) + ((s.zp + s.zm) - c2u);
+  const T lap = (((s.xp + s.xm) - T(2) * c) + ((s.yp + s.ym) - T(2) * c)) + ((s.zp + s.zm) - T(2) * c);
   o.Q = o.ax * o.ax + o.ay * o.ay + o.az * o.az;
   const T R = o.Q + k.reg;
   rcp_rsqrt(R, o.Rinv, o.rs);
@@ -439,7 +449,7 @@ __device__ __forceinline__ T trace_density_adjoint(const Stencil19<T>& s, const 
   const T trb = g1 + ctr;                          // df/dT~
   a.ub = trb * (fw.Q * fw.Rinv) * (p.lam * (T(3) * fw.c * fw.c - T(1)));
   // df/da_a / 2 = fac a_a
-  const T fac = (p.C6 + (T(0.5) * p.C4) * tr * fw.rs) + (fw.sw * trb) * (k.reg * fw.Rinv);
+  const T fac = (p.C6 + p.hC4 * tr * fw.rs) + (fw.sw * trb) * (k.reg * fw.Rinv);
   a.hgx = fac * fw.ax;
   a.hgy = fac * fw.ay;
   T hgz = fac * fw.az;
@@ -470,7 +480,6 @@ __device__ __forceinline__ T voxel_density_adjoint_body(const Stencil19<T>& s, R
   T f, hrhob, trb0, bxx, byy, bzz, cqh;
   const T rs = fw.rs;
   const T rho = fw.R * rs;                         // 2h rho
-  const T c1x2 = p.C1 + p.C1;
   // f~ = C1 N~ + T~ g1 + C5 rho~ S~ + C6 Q with g1 = C2 T~ + C3 S~ + C4 rho~, so
   // df/dT~ = g1 + C2 T~ (the product C2 T~ serves both)
   const T ctr = p.C2 * tr;
@@ -478,12 +487,12 @@ __device__ __forceinline__ T voxel_density_adjoint_body(const Stencil19<T>& s, R
     const T g1 = ctr + p.C4 * rho;
     f = p.C1 * fw.n2 + tr * g1 + p.C6 * fw.Q;
     // ---- reverse sweep ----
-    hrhob = (T(0.5) * p.C4) * tr;                  // df/drho~ / 2
+    hrhob = p.hC4 * tr;                            // df/drho~ / 2
     trb0 = g1 + ctr;
-    bxx = c1x2 * fw.mxx + trb0;
-    byy = c1x2 * fw.myy + trb0;
-    bzz = c1x2 * fw.mzz + trb0;
-    cqh = T(0.5) * p.C1;
+    bxx = p.C1x2 * fw.mxx + trb0;
+    byy = p.C1x2 * fw.myy + trb0;
+    bzz = p.C1x2 * fw.mzz + trb0;
+    cqh = p.hC1;
   } else {
     T P, sig;
     softplus_xi(fw.X, p, P, sig);
@@ -496,17 +505,17 @@ __device__ __forceinline__ T voxel_density_adjoint_body(const Stencil19<T>& s, R
 
     // ---- reverse sweep ----
     const T Sb = p.C3 * tr + c5r;                  // df/dS~
-    hrhob = (T(0.5) * p.C4) * tr + (T(0.5) * p.C5) * S;   // df/drho~ / 2
+    hrhob = p.hC4 * tr + p.hC5 * S;                // df/drho~ / 2
     const T kap = Sb * sig * (T(0.5) * rsP);       // df/dX~  (dS~/dX~ = sig / (2S~); 0 where S~ = 0)
     const T kap2 = kap + kap;
     // df/dm_aa = 2 C1 m_aa + df/dT~ + 2 kap (2 m_aa - T~): the X~ part is
     // written with the difference formed in the forward chain, so no two
     // kap-sized terms cancel.
     trb0 = g1 + ctr;
-    bxx = c1x2 * fw.mxx + trb0 + kap2 * fw.dxx;
-    byy = c1x2 * fw.myy + trb0 + kap2 * fw.dyy;
-    bzz = c1x2 * fw.mzz + trb0 + kap2 * fw.dzz;
-    cqh = T(0.5) * p.C1 + kap;
+    bxx = p.C1x2 * fw.mxx + trb0 + kap2 * fw.dxx;
+    byy = p.C1x2 * fw.myy + trb0 + kap2 * fw.dyy;
+    bzz = p.C1x2 * fw.mzz + trb0 + kap2 * fw.dzz;
+    cqh = p.hC1 + kap;
   }
   // qh_ab = 2 df/do_ab = (C1/2 + kap) o_ab = -2 df/db_ab
   const T qxy = cqh * fw.oxy, qxz = cqh * fw.oxz, qyz = cqh * fw.oyz;

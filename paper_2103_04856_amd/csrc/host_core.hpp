@@ -312,6 +312,7 @@ fe::InstParams<T> inst_params(double h, double e, const double* a, double mu, co
   p.thx = T(theta[0]);
   p.thy = T(theta[1]);
   p.thz = T(theta[2]);
+  fe::set_multiples(p);
   return p;
 }
 
