@@ -231,16 +231,24 @@ __device__ __forceinline__ void write_partials(const SweepArgs<T>& a, int logica
 // wave adds the partials of blocks l, l + 64, l + 128, ... in that order, then
 // a butterfly over the wave combines the lanes. Each butterfly step adds a lane
 // and its partner, and the two orders of an addition agree bit for bit, so
-// every lane of every wave that calls this gets the same bits. Call from all
-// 64 lanes of a wave.
+// every lane of every wave that calls this gets the same bits. Eight loads of a
+// lane are in flight at once: a step's blocks wait for these sums before their
+// first plane (768 partials at 256^3). Call from all 64 lanes of a wave.
 __device__ __forceinline__ void instance_sums(const double* __restrict__ partials, int inst, int per_inst,
                                               double& sf, double& sm) {
+  constexpr int U = 8;
   const int lane = threadIdx.x % kWave;
-  const double* pp = partials + (size_t)inst * per_inst * 2;
+  const double2* pp = reinterpret_cast<const double2*>(partials) + (size_t)inst * per_inst;
   double f = 0.0, m = 0.0;
-  for (int k = lane; k < per_inst; k += kWave) {
-    f += pp[2 * k];
-    m += pp[2 * k + 1];
+  for (int k = lane; k < per_inst; k += U * kWave) {
+    double2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = k + u * kWave < per_inst ? pp[k + u * kWave] : double2{0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      f += v[u].x;
+      m += v[u].y;
+    }
   }
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) {
@@ -365,6 +373,9 @@ __device__ __forceinline__ BlockTile block_tile(const SweepArgs<T>& a) {
 // BOX: only voxels inside [box_lo, box_hi) carry a density; the others (the
 // padding of a non-periodic field) have zero adjoints, and the gradient is
 // written at every voxel, padding included, for the caller to fold back.
+// EN: the energy of the swept field is wanted. Without it (the gradient of a
+// backward pass, every step or flow iteration whose energy nobody reads) the
+// density is not formed and partial [0] is 0.
 template <typename T, int NT, int MODE, bool SP>
 constexpr int sweep_min_waves() {
   // two FP64 blocks of 512 threads share a compute unit with up to 128 registers;
@@ -372,7 +383,8 @@ constexpr int sweep_min_waves() {
   return sizeof(T) == 8 && NT == 512 && MODE == kGrad && !SP ? 4 : 1;
 }
 
-template <typename T, int TX, int TY, int NT, int MODE, bool SP = false, bool BOX = false, int BODY = kBodyAny>
+template <typename T, int TX, int TY, int NT, int MODE, bool SP = false, bool BOX = false, int BODY = kBodyAny,
+          bool EN = true>
 __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad_sweep(SweepArgs<T> a) {
   constexpr int UX = TX + 4, UY = TY + 4;      // u window: interior + halo 2
   constexpr int RX = TX + 2, RY = TY + 2;      // adjoint ring: interior + 1
@@ -715,7 +727,7 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad
         // u of output plane p-1 at this voxel, read before the second barrier (its
         // slot takes plane p+2 in the next iteration)
         if (STEP) u_out[o] = st.zm;
-        if (out_plane && oin[o]) fpl += f;
+        if (EN && out_plane && oin[o]) fpl += f;
       }
     };
     if constexpr (COLS) {

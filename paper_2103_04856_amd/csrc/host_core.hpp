@@ -36,14 +36,13 @@ using SweepFn = void (*)(fe::SweepArgs<T>);
 
 constexpr int kBodies = 4;   // fe::SweepBody values
 
-// The sweep kernels of one launch shape: [fe::SweepBody] for the gradient, the
-// plain step and the Adam step (the single-body ones only for the leading
-// shapes; nullptr where not built).
+// The sweep kernels of one launch shape: [fe::SweepMode] (the gradient, the plain
+// step, the Adam step), [0] with the energy and [1] without, [fe::SweepBody]. The
+// single-body ones, and those without the energy, exist only for the leading
+// shapes; nullptr where not built.
 template <typename T>
 struct Kernels {
-  SweepFn<T> grad[kBodies] = {};
-  SweepFn<T> step[kBodies] = {};
-  SweepFn<T> adam[kBodies] = {};
+  SweepFn<T> fn[3][2][kBodies] = {};
   SweepFn<T> energy = nullptr;
 };
 
@@ -59,23 +58,28 @@ struct Variant {
   bool lead = false;   // a default candidate: chosen by the ring work its tiles cover a grid with
 };
 
+template <typename T, int TX, int TY, int NT, int MODE, int BODY>
+void add_body_kernels(Kernels<T>& k) {
+  k.fn[MODE][0][BODY] = fe::grad_sweep<T, TX, TY, NT, MODE, false, false, BODY>;
+  k.fn[MODE][1][BODY] = fe::grad_sweep<T, TX, TY, NT, MODE, false, false, BODY, false>;
+}
+
+template <typename T, int TX, int TY, int NT, int MODE, bool SP, bool BODIES>
+void add_mode_kernels(Kernels<T>& k) {
+  k.fn[MODE][0][fe::kBodyAny] = fe::grad_sweep<T, TX, TY, NT, MODE, SP>;
+  if constexpr (BODIES && !SP) {
+    add_body_kernels<T, TX, TY, NT, MODE, fe::kBodyNoS>(k);
+    add_body_kernels<T, TX, TY, NT, MODE, fe::kBodyFull>(k);
+    add_body_kernels<T, TX, TY, NT, MODE, fe::kBodyTrace>(k);
+  }
+}
+
 template <typename T, int TX, int TY, int NT, bool SP = false, bool BODIES = false>
 Kernels<T> make_kernels() {
   Kernels<T> k;
-  k.grad[fe::kBodyAny] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, SP>;
-  k.step[fe::kBodyAny] = fe::grad_sweep<T, TX, TY, NT, fe::kStepGD, SP>;
-  k.adam[fe::kBodyAny] = fe::grad_sweep<T, TX, TY, NT, fe::kStepAdam, SP>;
-  if constexpr (BODIES && !SP) {
-    k.grad[fe::kBodyNoS] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, false, fe::kBodyNoS>;
-    k.step[fe::kBodyNoS] = fe::grad_sweep<T, TX, TY, NT, fe::kStepGD, false, false, fe::kBodyNoS>;
-    k.adam[fe::kBodyNoS] = fe::grad_sweep<T, TX, TY, NT, fe::kStepAdam, false, false, fe::kBodyNoS>;
-    k.grad[fe::kBodyFull] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, false, fe::kBodyFull>;
-    k.step[fe::kBodyFull] = fe::grad_sweep<T, TX, TY, NT, fe::kStepGD, false, false, fe::kBodyFull>;
-    k.adam[fe::kBodyFull] = fe::grad_sweep<T, TX, TY, NT, fe::kStepAdam, false, false, fe::kBodyFull>;
-    k.grad[fe::kBodyTrace] = fe::grad_sweep<T, TX, TY, NT, fe::kGrad, false, false, fe::kBodyTrace>;
-    k.step[fe::kBodyTrace] = fe::grad_sweep<T, TX, TY, NT, fe::kStepGD, false, false, fe::kBodyTrace>;
-    k.adam[fe::kBodyTrace] = fe::grad_sweep<T, TX, TY, NT, fe::kStepAdam, false, false, fe::kBodyTrace>;
-  }
+  add_mode_kernels<T, TX, TY, NT, fe::kGrad, SP, BODIES>(k);
+  add_mode_kernels<T, TX, TY, NT, fe::kStepGD, SP, BODIES>(k);
+  add_mode_kernels<T, TX, TY, NT, fe::kStepAdam, SP, BODIES>(k);
   k.energy = fe::energy_sweep<T, TX, TY, NT, SP>;
   return k;
 }
@@ -101,10 +105,12 @@ SweepFn<T> body_kernel(const SweepFn<T>* f, int body) {
   return f[body] ? f[body] : f[fe::kBodyAny];
 }
 
-// The kernel of `kind` (a fe::SweepMode).
+// The kernel of `kind` (a fe::SweepMode); without the energy where such a kernel
+// is built and `energy` is false.
 template <typename T>
-SweepFn<T> sweep_kernel(const Kernels<T>& k, int kind, int body) {
-  return body_kernel<T>(kind == fe::kGrad ? k.grad : kind == fe::kStepGD ? k.step : k.adam, body);
+SweepFn<T> sweep_kernel(const Kernels<T>& k, int kind, int body, bool energy = true) {
+  const SweepFn<T> quiet = k.fn[kind][1][body];
+  return !energy && quiet ? quiet : body_kernel<T>(k.fn[kind][0], body);
 }
 
 // Static LDS of grad_sweep is (4 (TX+4)(TY+4) + 7 (TX+2)(TY+2)) sizeof(T) plus
@@ -453,15 +459,17 @@ Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, i
 // The kernel launch_sweep runs for `kind` (-1: energy only, else a
 // fe::SweepMode) with `variant` on this context.
 template <typename T>
-SweepFn<T> sweep_fn(const fe_ctx* c, const Variant& v, int kind) {
+SweepFn<T> sweep_fn(const fe_ctx* c, const Variant& v, int kind, bool energy = true) {
   if (c->use_box) return box_kernel_of<T>(v, c->body);
   const Kernels<T>& k = kernels_of<T>(v, c->use_cfield);
-  return kind < 0 ? k.energy : sweep_kernel<T>(k, kind, c->use_cfield ? (int)fe::kBodyAny : c->body);
+  return kind < 0 ? k.energy : sweep_kernel<T>(k, kind, c->use_cfield ? (int)fe::kBodyAny : c->body, energy);
 }
 
 // Blocks of that kernel one compute unit holds at once: its registers and LDS
 // decide it (the symmetric step body at 32 x 32 takes three, the bodies with the
-// S terms two), and the automatic z chunks follow it.
+// S terms two), and the automatic z chunks follow it. The kernel is the one with
+// the energy, also for launches without it: the sweeps of a step loop, whose
+// partials the next sweep reads, share one geometry.
 int launch_slots(const fe_ctx* c, int variant, int kind) {
   const Variant& v = variants()[variant];
   const void* fn = c->grid.dtype == FE_F32 ? (const void*)sweep_fn<float>(c, v, kind)
@@ -478,7 +486,7 @@ Geometry geometry(const fe_ctx* c, int variant, int lz_req, int kind) {
 
 bool has_sp(int v, int dtype) {
   const Variant& x = variants()[v];
-  return dtype == FE_F32 ? x.k32sp.grad[fe::kBodyAny] != nullptr : x.k64sp.grad[fe::kBodyAny] != nullptr;
+  return dtype == FE_F32 ? x.k32sp.fn[fe::kGrad][0][fe::kBodyAny] != nullptr : x.k64sp.fn[fe::kGrad][0][fe::kBodyAny] != nullptr;
 }
 
 bool has_box(int v, int dtype) {
@@ -540,10 +548,10 @@ double* partials_buf(fe_ctx* c, int i) { return c->d_partials + (size_t)i * 2 * 
 // kind: -1 energy only, else a fe::SweepMode. One launch; the block partials go
 // to `partials`. Steps add to src the shift formed from prev_partials (the
 // partials of the step that wrote src; null: no shift); Adam steps use the
-// step number t0 + t_add.
+// step number t0 + t_add. energy: whether the caller reads the energy.
 template <typename T>
 int launch_sweep(fe_ctx* c, hipStream_t s, int kind, const void* src, void* dst, const double* prev_partials,
-                 double* partials, const StepRule& rule, int t_add) {
+                 double* partials, const StepRule& rule, int t_add, bool energy) {
   const int vi = sweep_variant(c);
   const Geometry geo = geometry(c, vi, c->lz, kind);
   if ((size_t)geo.per_inst > c->max_blocks) return set_error(FE_EINVAL, "internal: partials workspace too small");
@@ -578,7 +586,7 @@ int launch_sweep(fe_ctx* c, hipStream_t s, int kind, const void* src, void* dst,
   const dim3 block((unsigned)v.nt);
   if (c->use_box && (kind != fe::kGrad || c->use_cfield))
     return set_error(FE_EINVAL, "internal: box sweeps are gradient-only");
-  const SweepFn<T> fn = sweep_fn<T>(c, v, kind);
+  const SweepFn<T> fn = sweep_fn<T>(c, v, kind, energy);
   if (c->use_box) {
     for (int i = 0; i < 3; ++i) {
       a.box_lo[i] = c->box_lo[i];
@@ -591,9 +599,10 @@ int launch_sweep(fe_ctx* c, hipStream_t s, int kind, const void* src, void* dst,
 }
 
 int sweep(fe_ctx* c, hipStream_t s, int kind, const void* src, void* dst, const double* prev_partials,
-          double* partials, const StepRule& rule, int t_add = 0) {
-  return c->grid.dtype == FE_F32 ? launch_sweep<float>(c, s, kind, src, dst, prev_partials, partials, rule, t_add)
-                                 : launch_sweep<double>(c, s, kind, src, dst, prev_partials, partials, rule, t_add);
+          double* partials, const StepRule& rule, int t_add = 0, bool energy = true) {
+  return c->grid.dtype == FE_F32
+             ? launch_sweep<float>(c, s, kind, src, dst, prev_partials, partials, rule, t_add, energy)
+             : launch_sweep<double>(c, s, kind, src, dst, prev_partials, partials, rule, t_add, energy);
 }
 
 // Per-instance totals of the sweep of `kind` that wrote `partials` (same launch
@@ -769,8 +778,9 @@ int run_steps(fe_ctx* c, void* u, const double* mass, const StepRule& rule, int 
   // Steps launched since the Adam step number was last advanced; step j of
   // them uses t0 + j.
   int pending = 0;
-  auto step = [&](hipStream_t s, const void* src, void* dst, const double* prev, double* out, int t_add) {
-    return sweep(c, s, rule.mode, src, dst, prev, out, rule, t_add);
+  auto step = [&](hipStream_t s, const void* src, void* dst, const double* prev, double* out, int t_add,
+                  bool energy) {
+    return sweep(c, s, rule.mode, src, dst, prev, out, rule, t_add, energy);
   };
   auto tick = [&](hipStream_t s, int n) { return adam && n > 0 ? adam_tick_launch(c, s, n) : FE_OK; };
 
@@ -778,14 +788,17 @@ int run_steps(fe_ctx* c, void* u, const double* mass, const StepRule& rule, int 
   // that the partials of its predecessor give. The rest come in pairs A -> u
   // (partials P1), u -> A (partials P0): whole blocks of kGraphPairs pairs are
   // replayed from one captured graph (the same graph for any nsteps), the
-  // others launch directly.
-  int rc = step(c->stream, u, A, nullptr, P0, pending++);
-  if (rc) return rc;
+  // others launch directly. Only the last step's energy is reported, so only that
+  // step (and the last of each graph, which may be it) forms one.
   const int npairs = (nsteps - 1) / 2;
   const int gpairs = npairs >= kGraphPairs ? kGraphPairs : 0;
-  for (int i = 0; i < (gpairs ? npairs % gpairs : npairs); ++i) {
-    rc = step(c->stream, A, u, P0, P1, pending++);
-    if (rc == FE_OK) rc = step(c->stream, u, A, P1, P0, pending++);
+  const int direct = gpairs ? npairs % gpairs : npairs;
+  const bool odd = (nsteps - 1) % 2 != 0;
+  int rc = step(c->stream, u, A, nullptr, P0, pending++, nsteps == 1);
+  if (rc) return rc;
+  for (int i = 0; i < direct; ++i) {
+    rc = step(c->stream, A, u, P0, P1, pending++, false);
+    if (rc == FE_OK) rc = step(c->stream, u, A, P1, P0, pending++, !gpairs && !odd && i + 1 == direct);
     if (rc) return rc;
   }
   if (gpairs > 0) {
@@ -799,8 +812,8 @@ int run_steps(fe_ctx* c, void* u, const double* mass, const StepRule& rule, int 
       hipGraph_t graph = nullptr;
       FE_HIP(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
       for (int i = 0; i < gpairs && rc == FE_OK; ++i) {
-        rc = step(c->cap_stream, A, u, P0, P1, 2 * i);
-        if (rc == FE_OK) rc = step(c->cap_stream, u, A, P1, P0, 2 * i + 1);
+        rc = step(c->cap_stream, A, u, P0, P1, 2 * i, false);
+        if (rc == FE_OK) rc = step(c->cap_stream, u, A, P1, P0, 2 * i + 1, i + 1 == gpairs);
       }
       if (rc == FE_OK) rc = tick(c->cap_stream, 2 * gpairs);
       hipError_t ec = hipStreamEndCapture(c->cap_stream, &graph);
@@ -821,8 +834,8 @@ int run_steps(fe_ctx* c, void* u, const double* mass, const StepRule& rule, int 
   }
   const void* last = A;
   const double* last_p = P0;
-  if ((nsteps - 1) % 2) {
-    if ((rc = step(c->stream, A, u, P0, P1, pending++))) return rc;
+  if (odd) {
+    if ((rc = step(c->stream, A, u, P0, P1, pending++, true))) return rc;
     last = u;
     last_p = P1;
   }
@@ -1079,7 +1092,7 @@ int fe_grad_scaled_async(fe_ctx* c, const void* u, void* g, const double* gscale
                        c->grid.batch);
   FE_HIP(hipGetLastError());
   c->prm_active = c->d_prm_scaled;
-  const int rc = sweep(c, c->stream, fe::kGrad, u, g, nullptr, partials_buf(c, 0), none);
+  const int rc = sweep(c, c->stream, fe::kGrad, u, g, nullptr, partials_buf(c, 0), none, 0, false);
   c->prm_active = nullptr;
   return rc;
 }

@@ -121,10 +121,10 @@ int flow_field(fe_ctx* c, hipStream_t s, const void* A, T* out, double sigma_k, 
   return FE_OK;
 }
 
-// One iteration of Algorithm 1 on A (in place); the energy of its field stays
-// in the block partials (partials_buf 0) for finish_sums.
+// One iteration of Algorithm 1 on A (in place); with `energy`, the energy of its
+// field stays in the block partials (partials_buf 0) for finish_sums.
 template <typename T>
-int flow_iteration(fe_ctx* c, hipStream_t s, void* A, const FlowRule& fr) {
+int flow_iteration(fe_ctx* c, hipStream_t s, void* A, const FlowRule& fr, bool energy) {
   T* w0 = static_cast<T*>(c->d_w0);
   T* w1 = static_cast<T*>(c->d_w1);
   const fe::FieldDims d{c->grid.nx, c->grid.ny, c->grid.nz, c->grid.batch};
@@ -132,9 +132,9 @@ int flow_iteration(fe_ctx* c, hipStream_t s, void* A, const FlowRule& fr) {
   // ub = k * (div A + m0) in w0
   int rc = flow_field<T>(c, s, A, w0, fr.sigma_k, c->d_flow_clk, fr.beta1, fr.beta2);
   if (rc) return rc;
-  // gb = dF/du at ub, in w1 (the energy of ub stays in the block partials)
+  // gb = dF/du at ub, in w1
   const StepRule none{fe::kGrad, 0.0, 0.0, 0.0, 0.0};
-  rc = sweep(c, s, fe::kGrad, w0, w1, nullptr, partials_buf(c, 0), none);
+  rc = sweep(c, s, fe::kGrad, w0, w1, nullptr, partials_buf(c, 0), none, 0, energy);
   if (rc) return rc;
   const T inv2h = T(1.0 / (2.0 * c->grid.h));
   const fe::FlowClock* clk = c->d_flow_clk;
@@ -155,8 +155,9 @@ int flow_iteration(fe_ctx* c, hipStream_t s, void* A, const FlowRule& fr) {
   return FE_OK;
 }
 
-int flow_iteration_any(fe_ctx* c, hipStream_t s, void* A, const FlowRule& fr) {
-  return c->grid.dtype == FE_F32 ? flow_iteration<float>(c, s, A, fr) : flow_iteration<double>(c, s, A, fr);
+int flow_iteration_any(fe_ctx* c, hipStream_t s, void* A, const FlowRule& fr, bool energy) {
+  return c->grid.dtype == FE_F32 ? flow_iteration<float>(c, s, A, fr, energy)
+                                 : flow_iteration<double>(c, s, A, fr, energy);
 }
 
 int flow_reset_launch(fe_ctx* c) {
@@ -214,8 +215,11 @@ int fe_hminus_step(fe_ctx* c, void* A, const double* m0, double sigma_k, double 
   const FlowRule fr{sigma_k, lr, beta1, beta2, adam_eps};
   constexpr int kGraphIters = 8;
   const int gi = nsteps >= kGraphIters ? kGraphIters : 0;
-  for (int i = 0; i < (gi ? nsteps % gi : nsteps); ++i) {
-    int rc = flow_iteration_any(c, c->stream, A, fr);
+  // only the last iteration's energy is reported: it, and the last of each graph,
+  // which may be it, form one
+  const int direct = gi ? nsteps % gi : nsteps;
+  for (int i = 0; i < direct; ++i) {
+    int rc = flow_iteration_any(c, c->stream, A, fr, !gi && i + 1 == direct);
     if (rc) return rc;
   }
   if (gi > 0) {
@@ -226,7 +230,7 @@ int fe_hminus_step(fe_ctx* c, void* A, const double* m0, double sigma_k, double 
       hipGraph_t graph = nullptr;
       FE_HIP(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
       int rc = FE_OK;
-      for (int i = 0; i < gi && rc == FE_OK; ++i) rc = flow_iteration_any(c, c->cap_stream, A, fr);
+      for (int i = 0; i < gi && rc == FE_OK; ++i) rc = flow_iteration_any(c, c->cap_stream, A, fr, i + 1 == gi);
       hipError_t ec = hipStreamEndCapture(c->cap_stream, &graph);
       if (rc) {
         if (graph) (void)hipGraphDestroy(graph);
