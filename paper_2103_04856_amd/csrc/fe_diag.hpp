@@ -26,16 +26,11 @@ namespace fe {
 constexpr int kDiagMaxBins = 64;      // per-block histogram in LDS: 64 x 64 FP64 = 32 KiB
 constexpr int kDiagStats = 5;         // F_h, A_eps, |discrepancy| sum, min u, max u
 
-struct DiagInst {
-  double ca, cb, cw;                  // eps h / 8, h^3 / (4 eps), eps h / 4
-};
-
 template <typename T>
 struct DiagArgs {
-  const DiagInst* inst;               // [batch]
   T* curv;                            // [batch][4][nz][ny][nx] (H, K, kappa1, kappa2) or null
   double* hist;                       // [batch][nbins][nbins] or null
-  double* partials;                   // [batch][blocks per instance][kDiagStats]
+  double* partials;                   // [batch][blocks per instance][kDiagStats] (STATS only)
   int nbins;
   T kmax, bin_scale;                  // bin_scale = nbins / (2 kmax)
   T inv_h, inv_h2;
@@ -48,16 +43,29 @@ __device__ __forceinline__ int diag_bin(T k, T kmax, T scale, int nbins) {
   return i < nbins - 1 ? i : nbins - 1;
 }
 
+// x * x rounded, not contracted into what takes it (nor merged with another x * x
+// that is): the curvatures have the same bits whatever else a call asks for.
+template <typename T>
+__device__ __forceinline__ T rounded_square(T x) {
+#pragma clang fp contract(off)
+  __asm__("" : "+v"(x));
+  return x * x;
+}
+
 // Block = a TX x TY column tile and lz planes (as the energy sweep, halo 1).
-// Each block writes its kDiagStats partials; diag_finish reduces them.
-template <typename T, int TX, int TY, int NT>
+// STATS: the summary is wanted; each block writes its kDiagStats partials, which
+// diag_finish reduces. HIST: the histogram is wanted. Without both (the curvature
+// fields alone) no density is formed, a block takes 50 instead of 79 VGPRs and 11
+// instead of 43 KiB of LDS, and the stores set the pace: 256^3 FP32 92 -> 80 us per
+// call, 4.2 TB/s of the 20 B/voxel (a copy of 1 GiB runs at 5.1 TB/s).
+template <typename T, int TX, int TY, int NT, bool STATS, bool HIST>
 __global__ __launch_bounds__(NT) void diag_sweep(SweepArgs<T> a, DiagArgs<T> d) {
   constexpr int UX = TX + 2, UY = TY + 2;
   constexpr int NU = (UX * UY + NT - 1) / NT;
   constexpr int NO = (TX * TY + NT - 1) / NT;
   static_assert(NO == 1, "the curvatures held for one plane are one voxel per thread");
   __shared__ T su[4][UY * UX];                 // four plane slots: one barrier per plane
-  __shared__ double shist[kDiagMaxBins * kDiagMaxBins];
+  __shared__ double shist[HIST ? kDiagMaxBins * kDiagMaxBins : 1];
   __shared__ double sred[NT / kWave][kDiagStats];
 
   const int tid = threadIdx.x;
@@ -67,9 +75,9 @@ __global__ __launch_bounds__(NT) void diag_sweep(SweepArgs<T> a, DiagArgs<T> d) 
   const size_t vol = plane * a.nz;
   const T* srcb = a.src + (size_t)bt.inst * vol;
   const InstParams<T> prm = a.prm[bt.inst];
-  const DiagInst di = d.inst[bt.inst];
-  const int nb2 = d.hist ? d.nbins * d.nbins : 0;
-  for (int i = tid; i < nb2; i += NT) shist[i] = 0.0;
+  const int nb2 = HIST ? d.nbins * d.nbins : 0;
+  if constexpr (HIST)
+    for (int i = tid; i < nb2; i += NT) shist[i] = 0.0;
 
   // byte offsets within a plane (at most 4 GiB - 64 KiB): the u window, and this thread's
   // output voxels for the curvature fields
@@ -160,25 +168,27 @@ __global__ __launch_bounds__(NT) void diag_sweep(SweepArgs<T> a, DiagArgs<T> d) 
         const char* pp = reinterpret_cast<const char*>(su[sp]) + lo;
         const Forward<T> fw = forward_chain(load_stencil<T, UX>(pc, pm, pp),
                                             [&]() { return load_stencil<T, UX>(pc, pm, pp); }, prm, a.k);
-        const size_t gi = (size_t)p * plane + (size_t)(y0 + iy) * a.nx + (x0 + ix);
-        acc_f += double(density_of(
-            fw, a.cfield ? with_coeffs(prm, coeff_records(a.cfield)[(size_t)bt.inst * vol + gi]) : prm));
-        const T grad_part = T(di.ca) * fw.Q;
-        const T w2 = T(1) - fw.c * fw.c;
-        const T well_part = T(di.cb) * w2 * w2;
-        acc_area += double(grad_part + well_part);
-        acc_disc += double(grad_part > well_part ? grad_part - well_part : well_part - grad_part);
-        umin = fw.c < umin ? fw.c : umin;
-        umax = fw.c > umax ? fw.c : umax;
-        if (d.curv || d.hist) {
+        if constexpr (STATS) {
+          const size_t gi = (size_t)p * plane + (size_t)(y0 + iy) * a.nx + (x0 + ix);
+          acc_f += double(density_of(
+              fw, a.cfield ? with_coeffs(prm, coeff_records(a.cfield)[(size_t)bt.inst * vol + gi]) : prm));
+          const T grad_part = T(prm.ca) * fw.Q;
+          const T w2 = T(1) - fw.c * fw.c;
+          const T well_part = T(prm.cb) * w2 * w2;
+          acc_area += double(grad_part + well_part);
+          acc_disc += double(grad_part > well_part ? grad_part - well_part : well_part - grad_part);
+          umin = fw.c < umin ? fw.c : umin;
+          umax = fw.c > umax ? fw.c : umax;
+        }
+        if (!STATS || d.curv || HIST) {
           const T rs = fw.rs * d.inv_h;                    // 1 / (h sqrt R)
           const T sq = fw.X > T(0) ? sqrt_t(fw.X) : T(0);
           k1 = (fw.tr + sq) * rs;
           k2 = (fw.tr - sq) * rs;
           cH = T(2) * fw.tr * rs;
-          cK = T(2) * (fw.tr * fw.tr - fw.n2) * (d.inv_h2 * rcp_t(fw.R));
-          if (d.hist) {
-            const double wgt = di.cw * double(fw.Q);
+          cK = T(2) * (rounded_square(fw.tr) - fw.n2) * (d.inv_h2 * rcp_t(fw.R));
+          if constexpr (HIST) {
+            const double wgt = prm.cw * double(fw.Q);
             if (wgt != 0.0) {
               const int bin = diag_bin(k1, d.kmax, d.bin_scale, d.nbins) * d.nbins +
                               diag_bin(k2, d.kmax, d.bin_scale, d.nbins);
@@ -200,35 +210,36 @@ __global__ __launch_bounds__(NT) void diag_sweep(SweepArgs<T> a, DiagArgs<T> d) 
     }
   }
   if (kend > k0) store_held(kend - 1, true);
-  if (run_bin >= 0) unsafeAtomicAdd(&shist[run_bin], run_w);
-
-  // block reduction of the five statistics
-  double v[kDiagStats] = {acc_f, acc_area, acc_disc, double(umin), double(umax)};
+  if constexpr (STATS) {
+    // block reduction of the five statistics
+    double v[kDiagStats] = {acc_f, acc_area, acc_disc, double(umin), double(umax)};
 #pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) {
-    v[0] += __shfl_xor(v[0], off, kWave);
-    v[1] += __shfl_xor(v[1], off, kWave);
-    v[2] += __shfl_xor(v[2], off, kWave);
-    v[3] = fmin(v[3], __shfl_xor(v[3], off, kWave));
-    v[4] = fmax(v[4], __shfl_xor(v[4], off, kWave));
-  }
-  const int lane = tid % kWave, wv = tid / kWave;
-  if (lane == 0)
-    for (int i = 0; i < kDiagStats; ++i) sred[wv][i] = v[i];
-  __syncthreads();
-  if (tid == 0) {
-    double r[kDiagStats] = {0.0, 0.0, 0.0, INFINITY, -INFINITY};
-    for (int i = 0; i < NT / kWave; ++i) {
-      r[0] += sred[i][0];
-      r[1] += sred[i][1];
-      r[2] += sred[i][2];
-      r[3] = fmin(r[3], sred[i][3]);
-      r[4] = fmax(r[4], sred[i][4]);
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+      v[0] += __shfl_xor(v[0], off, kWave);
+      v[1] += __shfl_xor(v[1], off, kWave);
+      v[2] += __shfl_xor(v[2], off, kWave);
+      v[3] = fmin(v[3], __shfl_xor(v[3], off, kWave));
+      v[4] = fmax(v[4], __shfl_xor(v[4], off, kWave));
     }
-    double* out = d.partials + (size_t)bt.logical * kDiagStats;
-    for (int i = 0; i < kDiagStats; ++i) out[i] = r[i];
+    const int lane = tid % kWave, wv = tid / kWave;
+    if (lane == 0)
+      for (int i = 0; i < kDiagStats; ++i) sred[wv][i] = v[i];
+    __syncthreads();
+    if (tid == 0) {
+      double r[kDiagStats] = {0.0, 0.0, 0.0, INFINITY, -INFINITY};
+      for (int i = 0; i < NT / kWave; ++i) {
+        r[0] += sred[i][0];
+        r[1] += sred[i][1];
+        r[2] += sred[i][2];
+        r[3] = fmin(r[3], sred[i][3]);
+        r[4] = fmax(r[4], sred[i][4]);
+      }
+      double* out = d.partials + (size_t)bt.logical * kDiagStats;
+      for (int i = 0; i < kDiagStats; ++i) out[i] = r[i];
+    }
   }
-  if (d.hist) {
+  if constexpr (HIST) {
+    if (run_bin >= 0) unsafeAtomicAdd(&shist[run_bin], run_w);
     __syncthreads();
     double* gh = d.hist + (size_t)bt.inst * nb2;
     for (int i = tid; i < nb2; i += NT)

@@ -48,6 +48,7 @@ struct InstParams {
   T C1x2, hC1, hC4, hC5;       // 2 C1, C1 / 2, C4 / 2, C5 / 2
   T Co;                        // orientation term of Sec. 5.2: h^3 eps mu / (4h^2) (0: off)
   T thx, thy, thz;             // its direction theta
+  double ca, cb, cw;           // diagnostics: eps h / 8, h^3 / (4 eps), eps h / 4
 };
 
 // The multiples of the coefficients that the adjoint takes, kept in the table so

@@ -246,7 +246,7 @@ struct fe_ctx {
   void* d_am1 = nullptr;              // H^-1 flow: Adam moments of A ([batch][3] fields each)
   void* d_am2 = nullptr;
   fe::FlowClock* d_flow_clk = nullptr; // H^-1 flow: Adam step number and bias corrections (device)
-  double* d_diag = nullptr;           // diagnostics: per-instance constants, stats, block partials
+  double* d_diag = nullptr;           // diagnostics: stats, block partials
   size_t diag_bytes = 0;
   void* d_cfield = nullptr;           // scaled coefficient field, [batch][nz][ny][nx] records of six (Sec. 5.2)
   bool use_cfield = false;
@@ -318,6 +318,9 @@ fe::InstParams<T> inst_params(double h, double e, const double* a, double mu, co
   p.thx = T(theta[0]);
   p.thy = T(theta[1]);
   p.thz = T(theta[2]);
+  p.ca = e * h / 8.0;
+  p.cb = h * h * h / (4.0 * e);
+  p.cw = e * h / 4.0;
   fe::set_multiples(p);
   return p;
 }

@@ -7,6 +7,18 @@ namespace {
 // The diagnostics sweep: one tile shape for both precisions.
 constexpr int kDiagTX = 64, kDiagTY = 8, kDiagNT = 512;
 
+// The kernel for what a call asks for.
+template <typename T>
+using DiagFn = void (*)(fe::SweepArgs<T>, fe::DiagArgs<T>);
+
+template <typename T>
+DiagFn<T> diag_kernel(bool stats, bool hist) {
+  if (stats) return hist ? fe::diag_sweep<T, kDiagTX, kDiagTY, kDiagNT, true, true>
+                         : fe::diag_sweep<T, kDiagTX, kDiagTY, kDiagNT, true, false>;
+  return hist ? fe::diag_sweep<T, kDiagTX, kDiagTY, kDiagNT, false, true>
+              : fe::diag_sweep<T, kDiagTX, kDiagTY, kDiagNT, false, false>;
+}
+
 template <typename T>
 int diagnostics(fe_ctx* c, const void* u, void* curv, double* hist, int nbins, double kmax, double* stats) {
   const int B = c->grid.batch;
@@ -15,15 +27,14 @@ int diagnostics(fe_ctx* c, const void* u, void* curv, double* hist, int nbins, d
   // blocks, one round of three per CU, where 32-plane chunks gave 1024 blocks and
   // a last round a third full
   int slots = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&slots, (const void*)fe::diag_sweep<T, kDiagTX, kDiagTY, kDiagNT>,
-                                                   kDiagNT, 0) != hipSuccess ||
-      slots < 1)
+  const DiagFn<T> fn = diag_kernel<T>(stats != nullptr, hist != nullptr);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&slots, (const void*)fn, kDiagNT, 0) != hipSuccess || slots < 1)
     slots = 1;
   const int lz = halo1_chunk((long)ntx * nty * B, c->grid.nz, c->num_cu, slots);
   const int nzc = ceil_div(c->grid.nz, lz);
   const size_t per_inst = (size_t)ntx * nty * nzc;
-  // layout of d_diag: DiagInst[B] | stats[B][5] | partials[B][per_inst][5]
-  const size_t need = sizeof(fe::DiagInst) * B + sizeof(double) * fe::kDiagStats * B * (1 + per_inst);
+  // layout of d_diag: stats[B][5] | partials[B][per_inst][5]
+  const size_t need = stats ? sizeof(double) * fe::kDiagStats * B * (1 + per_inst) : 0;
   if (c->diag_bytes < need) {
     if (c->d_diag) (void)hipFree(c->d_diag);
     c->d_diag = nullptr;
@@ -35,15 +46,8 @@ int diagnostics(fe_ctx* c, const void* u, void* curv, double* hist, int nbins, d
     c->diag_bytes = need;
   }
   const double h = c->grid.h;
-  std::vector<fe::DiagInst> di(B);
-  for (int b = 0; b < B; ++b) {
-    const double eps = c->eps[b];
-    di[b] = fe::DiagInst{eps * h / 8.0, h * h * h / (4.0 * eps), eps * h / 4.0};
-  }
-  fe::DiagInst* d_inst = reinterpret_cast<fe::DiagInst*>(c->d_diag);
-  double* d_stats = reinterpret_cast<double*>(d_inst + B);
-  double* d_part = d_stats + (size_t)fe::kDiagStats * B;
-  FE_HIP(hipMemcpyAsync(d_inst, di.data(), sizeof(fe::DiagInst) * B, hipMemcpyHostToDevice, c->stream));
+  double* d_stats = c->d_diag;
+  double* d_part = stats ? d_stats + (size_t)fe::kDiagStats * B : nullptr;
   if (hist) {
     const int n = B * nbins * nbins;
     hipLaunchKernelGGL(fe::fill_f64, dim3(ceil_div(n, 64)), dim3(64), 0, c->stream, hist, n, 0.0);
@@ -62,7 +66,6 @@ int diagnostics(fe_ctx* c, const void* u, void* curv, double* hist, int nbins, d
   a.lz = lz;
   a.batch = B;
   fe::DiagArgs<T> d{};
-  d.inst = d_inst;
   d.curv = static_cast<T*>(curv);
   d.hist = hist;
   d.partials = d_part;
@@ -71,12 +74,12 @@ int diagnostics(fe_ctx* c, const void* u, void* curv, double* hist, int nbins, d
   d.bin_scale = T(hist ? nbins / (2.0 * kmax) : 0.0);
   d.inv_h = T(1.0 / h);
   d.inv_h2 = T(1.0 / (h * h));
-  hipLaunchKernelGGL((fe::diag_sweep<T, kDiagTX, kDiagTY, kDiagNT>), dim3((unsigned)(per_inst * B)),
-                     dim3(kDiagNT), 0, c->stream, a, d);
-  hipLaunchKernelGGL(fe::diag_finish, dim3(B), dim3(256), 0, c->stream, (const double*)d_part, (int)per_inst,
-                     d_stats);
+  hipLaunchKernelGGL(fn, dim3((unsigned)(per_inst * B)), dim3(kDiagNT), 0, c->stream, a, d);
   FE_HIP(hipGetLastError());
   if (stats) {
+    hipLaunchKernelGGL(fe::diag_finish, dim3(B), dim3(256), 0, c->stream, (const double*)d_part, (int)per_inst,
+                       d_stats);
+    FE_HIP(hipGetLastError());
     FE_HIP(hipMemcpyAsync(stats, d_stats, sizeof(double) * fe::kDiagStats * B, hipMemcpyDeviceToHost, c->stream));
     FE_HIP(hipStreamSynchronize(c->stream));
   }
