@@ -28,7 +28,24 @@ constexpr int kBlurMaxR = 16;   // at most 33 taps: blur widths up to 4 voxels
 template <typename T>
 struct BlurTaps {
   T w[2 * kBlurMaxR + 1];       // w[r + j], j = -r..r, even, summing to 1
+  T c[kBlurMaxR + 1];           // c[k] = w_k + w_{k+1} + ... + w_r (kAdjoint at a face)
   int r;
+};
+
+// What a blur pass reads beyond the ends of an axis. kPeriodic wraps. The others
+// work on a box inside a field with one more sample on every side (Algorithm 2):
+// kReplicate reads the nearest box voxel; kAdjoint is its transpose, which reads
+// zero there and adds onto a face voxel what the samples copying it would
+// receive: out(face) = sum_k c_k in(face + k inwards). Both write box voxels only,
+// so no pass fills, blurs or folds a margin as wide as the kernel.
+enum BlurEdge { kPeriodic = 0, kReplicate = 1, kAdjoint = 2 };
+
+// The box [lo, lo + n) along every axis of such a field, and where a pass writes box
+// voxel (x, y, z): orow, oplane and ooff place it in a field or in a dense box.
+struct EdgeBox {
+  int lo;
+  int nx, ny, nz;
+  size_t orow, oplane, ooff;
 };
 
 struct FieldDims {
@@ -98,14 +115,54 @@ __device__ __forceinline__ Tile3 xcd_tile() {
   return t;
 }
 
+// The largest radius of a pass for radius R (-1: any).
+template <int R>
+constexpr int radius_bound() { return R >= 0 ? R : kBlurMaxR; }
+
+__device__ __forceinline__ int clamp_index(int v, int n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
+
+// The derivative at box voxel (x, y) of the plane z (field index) with what the
+// sweep left one sample outside the box added onto the voxel that sample copies
+// (the transpose of replicating by one): the sums run in increasing index order.
+template <typename T>
+__device__ __forceinline__ T folded(const T* __restrict__ f, const FieldDims& d, const EdgeBox& e, int x, int y,
+                                    int z) {
+  const int zb = z - e.lo;
+  const size_t plane = (size_t)d.nx * d.ny;
+  const T* p = f + (size_t)z * plane + (size_t)(e.lo + y) * d.nx + (e.lo + x);
+  const int za = zb == 0 ? -1 : 0, ze = zb == e.nz - 1 ? 1 : 0;
+  const int ya = y == 0 ? -1 : 0, ye = y == e.ny - 1 ? 1 : 0;
+  const int xa = x == 0 ? -1 : 0, xe = x == e.nx - 1 ? 1 : 0;
+  if (!(za | ze | ya | ye | xa | xe)) return *p;
+  T acc = T(0);
+  for (int k = za; k <= ze; ++k)
+    for (int j = ya; j <= ye; ++j)
+      for (int i = xa; i <= xe; ++i) acc += p[(long)k * (long)plane + (long)j * d.nx + i];
+  return acc;
+}
+
+// kAdjoint at a face: sum_k c_k v[k], k = 0..r inwards from the near face, v[-k] from
+// the far one. A voxel that is both faces (a box one voxel thick, zeros around it)
+// takes both sums, with its own weight once.
+template <typename T, int R>
+__device__ __forceinline__ T face_dot(const BlurTaps<T>& k, const T* v, bool near, bool far) {
+  const int r = R >= 0 ? R : k.r;
+  T acc = T(0);
+#pragma unroll
+  for (int j = 0; j <= radius_bound<R>(); ++j)
+    if (R >= 0 || j <= k.r) {
+      if (near) acc += k.c[j] * v[j];
+      if (far) acc += k.c[j] * v[-j];
+    }
+  if (near && far) acc -= k.w[r] * v[0];
+  return acc;
+}
+
 // The blur kernels take the radius as a template argument R for the common
 // widths (sigma_k = 1 and 2 give r = 4 and 8), so their tap loops are fixed;
 // R = -1 is the general form, whose loops run to the largest radius under a
 // uniform guard. Either way the taps are read at fixed offsets (kernel
 // arguments in scalar registers), never indexed at run time.
-template <int R>
-constexpr int radius_bound() { return R >= 0 ? R : kBlurMaxR; }
-
 // sum_j w_j v[j * step], j = 0..2r
 template <typename T, int R>
 __device__ __forceinline__ T taps_dot(const BlurTaps<T>& k, const T* v, int step) {
@@ -130,11 +187,12 @@ __device__ __forceinline__ T taps_dot(const BlurTaps<T>& k, const T* v, int step
 constexpr int kBlurRows = 16;
 constexpr int kRowsMax = 128;   // ROWS: the longest staged row, nx + 2r
 
-template <typename T, bool DIV, int R = -1, bool ROWS = false>
+template <typename T, bool DIV, int R = -1, bool ROWS = false, int EDGE = kPeriodic>
 __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __restrict__ out,
                                               const double* __restrict__ m0, const T* __restrict__ mfield,
                                               FieldDims d, T inv2h, BlurTaps<T> k, FlowClock* __restrict__ clk,
-                                              double beta1, double beta2) {
+                                              double beta1, double beta2, EdgeBox e) {
+  static_assert(!DIV || EDGE == kPeriodic, "the divergence is periodic");
   constexpr int kW = ROWS ? kRowsMax : 64 + 2 * kBlurMaxR;
   constexpr int kPer = (kW + 63) / 64;          // segment elements per thread and row
   constexpr int kR = kBlurRows / 4;             // rows per thread
@@ -147,12 +205,14 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
     clk->bc2 = 1.0 / (1.0 - ::pow(beta2, (double)t));
   }
   const Tile3 t = xcd_tile();
-  const int z = t.z % d.nz, b = t.z / d.nz;
+  // with a box, rows, planes and x count from its corner
+  const int nx = EDGE == kPeriodic ? d.nx : e.nx, ny = EDGE == kPeriodic ? d.ny : e.ny;
+  const int z = EDGE == kPeriodic ? t.z % d.nz : e.lo + t.z, b = EDGE == kPeriodic ? t.z / d.nz : 0;
   const int x0 = ROWS ? 0 : t.x * 64;
   const size_t plane = (size_t)d.nx * d.ny, vol = plane * d.nz;
   const T* base = in + (size_t)b * (DIV ? 3 : 1) * vol;
   const int r = R >= 0 ? R : k.r;
-  const int nseg = (ROWS ? d.nx : 64) + 2 * r;
+  const int nseg = (ROWS ? nx : 64) + 2 * r;
   // A wave's rows are uniform (threadIdx.y is the wave), so the row pointers
   // live in scalar registers and every load takes a 32-bit lane offset: the
   // segment's x positions and their periodic x neighbours, formed once.
@@ -160,17 +220,18 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
   int xs[kPer], xp[kPer], xm[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const int x = wrap_any(x0 - r + (int)threadIdx.x + 64 * j, d.nx);
-    xs[j] = x;
-    xp[j] = wrap_up(x + 1, d.nx);
-    xm[j] = wrap_down(x - 1, d.nx);
+    const int x = x0 - r + (int)threadIdx.x + 64 * j;
+    xs[j] = EDGE == kPeriodic ? wrap_any(x, nx) : EDGE == kReplicate ? clamp_index(x, nx) : x;
+    xp[j] = wrap_up(xs[j] + 1, nx);
+    xm[j] = wrap_down(xs[j] - 1, nx);
   }
   T v[kR][kPer][7];          // the non-DIV form uses [0] only; [6] holds m(x)
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
     const int y = t.y * kBlurRows + wy + 4 * i;
-    if (y >= d.ny) continue;
-    const T* row = base + (size_t)z * plane + (size_t)y * d.nx;
+    if (y >= ny) continue;
+    const T* row = EDGE == kPeriodic ? base + (size_t)z * plane + (size_t)y * d.nx
+                                     : base + (size_t)z * plane + (size_t)(e.lo + y) * d.nx + e.lo;
     // the A_y rows y +- 1 and the A_z rows of the planes z +- 1 (DIV only)
     const T* rowyp = DIV ? base + vol + (size_t)z * plane + (size_t)wrap_up(y + 1, d.ny) * d.nx : row;
     const T* rowym = DIV ? base + vol + (size_t)z * plane + (size_t)wrap_down(y - 1, d.ny) * d.nx : row;
@@ -179,8 +240,8 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
     const T* rowm = (DIV && mfield) ? mfield + (size_t)b * vol + (size_t)z * plane + (size_t)y * d.nx : row;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const int e = threadIdx.x + 64 * j;
-      if (e >= nseg) continue;
+      const int c = threadIdx.x + 64 * j;
+      if (c >= nseg) continue;
       if (DIV) {
         v[i][j][0] = load_u32(row, xp[j]);
         v[i][j][1] = load_u32(row, xm[j]);
@@ -189,6 +250,8 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
         v[i][j][4] = load_u32(rowzp, xs[j]);
         v[i][j][5] = load_u32(rowzm, xs[j]);
         if (mfield) v[i][j][6] = load_u32(rowm, xs[j]);
+      } else if (EDGE == kAdjoint) {
+        v[i][j][0] = xs[j] >= 0 && xs[j] < nx ? folded(in, d, e, xs[j], y, z) : T(0);
       } else {
         v[i][j][0] = load_u32(row, xs[j]);
       }
@@ -198,17 +261,17 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
     const int y = t.y * kBlurRows + wy + 4 * i;
-    if (y >= d.ny) continue;
+    if (y >= ny) continue;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const int e = threadIdx.x + 64 * j;
-      if (e >= nseg) continue;
+      const int c = threadIdx.x + 64 * j;
+      if (c >= nseg) continue;
       if (DIV)
-        s[wy + 4 * i][e] =
+        s[wy + 4 * i][c] =
             (mfield ? v[i][j][6] : mass) +
             ((v[i][j][0] - v[i][j][1]) + (v[i][j][2] - v[i][j][3]) + (v[i][j][4] - v[i][j][5])) * inv2h;
       else
-        s[wy + 4 * i][e] = v[i][j][0];
+        s[wy + 4 * i][c] = v[i][j][0];
     }
   }
   __syncthreads();
@@ -216,13 +279,16 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
   for (int jo = 0; jo < (ROWS ? kPer : 1); ++jo) {
     const int xo = threadIdx.x + 64 * jo;       // output position in the tile
     const int x = x0 + xo;
-    if (x >= d.nx) break;
+    if (x >= nx) break;
 #pragma unroll
     for (int i = 0; i < kR; ++i) {
       const int y = t.y * kBlurRows + wy + 4 * i;
-      if (y >= d.ny) continue;
-      T* orow = out + (size_t)b * vol + (size_t)z * plane + (size_t)y * d.nx;
-      orow[x] = taps_dot<T, R>(k, &s[wy + 4 * i][xo], 1);
+      if (y >= ny) continue;
+      T* orow = EDGE == kPeriodic ? out + (size_t)b * vol + (size_t)z * plane + (size_t)y * d.nx
+                                  : out + e.ooff + (size_t)t.z * e.oplane + (size_t)y * e.orow;
+      orow[x] = EDGE == kAdjoint && (x == 0 || x == nx - 1)
+                    ? face_dot<T, R>(k, &s[wy + 4 * i][xo + r], x == 0, x == nx - 1)
+                    : taps_dot<T, R>(k, &s[wy + 4 * i][xo], 1);
     }
   }
 }
@@ -237,48 +303,81 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
 // ceil(n_axis / kAxisChunk), batch).
 constexpr int kAxisChunk = 16;
 
-template <typename T, int AXIS, int R = -1>
+template <typename T, int AXIS, int R = -1, int EDGE = kPeriodic>
 __global__ __launch_bounds__(256) void blur_axis(const T* __restrict__ in, T* __restrict__ out, FieldDims d,
-                                                 BlurTaps<T> k) {
+                                                 BlurTaps<T> k, EdgeBox e) {
   constexpr int kWin = kAxisChunk + 2 * radius_bound<R>();
   const int r = R >= 0 ? R : k.r;
   const Tile3 t = xcd_tile();
-  const int n_axis = AXIS == 1 ? d.ny : d.nz;
   const size_t plane = (size_t)d.nx * d.ny, vol = plane * d.nz;
-  const unsigned nflat = AXIS == 2 ? (unsigned)plane : (unsigned)d.nz * (unsigned)d.nx;
   const unsigned q = (unsigned)t.x * 256u + threadIdx.x;
-  if (q >= nflat) return;
   const int p0 = t.y * kAxisChunk;
-  const T* inb = in + (size_t)t.z * vol;
-  T* outb = out + (size_t)t.z * vol;
   T v[kWin];
-  if (AXIS == 2) {
+  if (EDGE == kPeriodic) {
+    const int n_axis = AXIS == 1 ? d.ny : d.nz;
+    const unsigned nflat = AXIS == 2 ? (unsigned)plane : (unsigned)d.nz * (unsigned)d.nx;
+    if (q >= nflat) return;
+    const T* inb = in + (size_t)t.z * vol;
+    T* outb = out + (size_t)t.z * vol;
+    if (AXIS == 2) {
 #pragma unroll
-    for (int i = 0; i < kWin; ++i)
-      if (R >= 0 || i < kAxisChunk + 2 * r) v[i] = load_u32(inb + (size_t)wrap_any(p0 - r + i, n_axis) * plane, q);
+      for (int i = 0; i < kWin; ++i)
+        if (R >= 0 || i < kAxisChunk + 2 * r) v[i] = load_u32(inb + (size_t)wrap_any(p0 - r + i, n_axis) * plane, q);
 #pragma unroll
-    for (int o = 0; o < kAxisChunk; ++o) {
-      if (p0 + o >= n_axis) break;
-      T acc = T(0);
+      for (int o = 0; o < kAxisChunk; ++o) {
+        if (p0 + o >= n_axis) break;
+        store_u32(outb + (size_t)(p0 + o) * plane, q, taps_dot<T, R>(k, v + o, 1));
+      }
+    } else {
+      const unsigned zq = q / (unsigned)d.nx, x = q - zq * (unsigned)d.nx;
+      const size_t lane = (size_t)zq * plane + x;
 #pragma unroll
-      for (int j = 0; j <= 2 * radius_bound<R>(); ++j)
-        if (R >= 0 || j <= 2 * r) acc += k.w[j] * v[o + j];
-      store_u32(outb + (size_t)(p0 + o) * plane, q, acc);
+      for (int i = 0; i < kWin; ++i)
+        if (R >= 0 || i < kAxisChunk + 2 * r) v[i] = inb[lane + (size_t)wrap_any(p0 - r + i, n_axis) * d.nx];
+#pragma unroll
+      for (int o = 0; o < kAxisChunk; ++o) {
+        if (p0 + o >= n_axis) break;
+        outb[lane + (size_t)(p0 + o) * d.nx] = taps_dot<T, R>(k, v + o, 1);
+      }
     }
   } else {
-    const unsigned zq = q / (unsigned)d.nx, x = q - zq * (unsigned)d.nx;
-    const size_t lane = (size_t)zq * plane + x;
+    // columns of the box: for z its voxels of a plane, for y the x values of every plane
+    const int n_axis = AXIS == 1 ? e.ny : e.nz;
+    if (q >= (unsigned)e.nx * (unsigned)(AXIS == 2 ? e.ny : e.nz)) return;
+    const unsigned s = q / (unsigned)e.nx, x = q - s * (unsigned)e.nx;     // s: y (for z) or z (for y)
+    const size_t step = AXIS == 2 ? plane : (size_t)d.nx, other = AXIS == 2 ? (size_t)d.nx : plane;
+    const T* col = in + (size_t)(e.lo + (int)s) * other + (e.lo + (int)x) + (size_t)e.lo * step;
+    T* ocol = out + e.ooff + (size_t)s * (AXIS == 2 ? e.orow : e.oplane) + x;
+    const size_t ostep = AXIS == 2 ? e.oplane : e.orow;
 #pragma unroll
     for (int i = 0; i < kWin; ++i)
-      if (R >= 0 || i < kAxisChunk + 2 * r) v[i] = inb[lane + (size_t)wrap_any(p0 - r + i, n_axis) * d.nx];
+      if (R >= 0 || i < kAxisChunk + 2 * r) {
+        const int p = p0 - r + i;
+        if (EDGE == kReplicate) v[i] = col[(size_t)clamp_index(p, n_axis) * step];
+        else v[i] = p >= 0 && p < n_axis ? col[(size_t)p * step] : T(0);
+      }
 #pragma unroll
     for (int o = 0; o < kAxisChunk; ++o) {
-      if (p0 + o >= n_axis) break;
-      T acc = T(0);
-#pragma unroll
-      for (int j = 0; j <= 2 * radius_bound<R>(); ++j)
-        if (R >= 0 || j <= 2 * r) acc += k.w[j] * v[o + j];
-      outb[lane + (size_t)(p0 + o) * d.nx] = acc;
+      const int p = p0 + o;
+      if (p >= n_axis) break;
+      T acc;
+      if (EDGE == kAdjoint && (p == 0 || p == n_axis - 1)) {
+        if constexpr (R >= 0) {
+          acc = face_dot<T, R>(k, v + o + R, p == 0, p == n_axis - 1);
+        } else {
+          // any radius: the window is indexed at run time only in memory
+          const bool near = p == 0, far = p == n_axis - 1;
+          acc = T(0);
+          for (int j = 0; j <= r; ++j) {
+            if (near && p + j < n_axis) acc += k.c[j] * col[(size_t)(p + j) * step];
+            if (far && p - j >= 0) acc += k.c[j] * col[(size_t)(p - j) * step];
+          }
+          if (near && far) acc -= k.w[r] * col[(size_t)p * step];
+        }
+      } else {
+        acc = taps_dot<T, R>(k, v + o, 1);
+      }
+      ocol[(size_t)p * ostep] = acc;
     }
   }
 }
@@ -299,14 +398,15 @@ __global__ __launch_bounds__(256) void blur_axis(const T* __restrict__ in, T* __
 // where two 64-wide tiles take 32.
 constexpr int kXYRows = 32;
 
-template <typename T, int R, bool ROWS = false>
+template <typename T, int R, bool ROWS = false, int EDGE = kPeriodic>
 __global__ __launch_bounds__(512) void blur_xy(const T* __restrict__ in, T* __restrict__ out, FieldDims d,
-                                               BlurTaps<T> k) {
+                                               BlurTaps<T> k, EdgeBox e) {
   static_assert(R > 0 && 2 * R <= 64 && R % 2 == 0, "blur_xy needs a fixed even radius");
   constexpr int NT = 512;
   constexpr int OUT = 4;                        // outputs per thread and pass
   // staged row width; ROWS: up to 128 staged, plus the 3 a ragged last quad reads past them
-  constexpr int W = ROWS ? kRowsMax + OUT : 64 + 2 * R, H = kXYRows + 2 * R;
+  constexpr int X1 = EDGE == kAdjoint && !ROWS;   // one more column: the sample beyond a far face in the last one
+  constexpr int W = ROWS ? kRowsMax + OUT : 64 + 2 * R + X1, H = kXYRows + 2 * R;
   constexpr int WM = ROWS ? kRowsMax : 64;      // x-blurred row width
   static_assert(kXYRows == OUT * (NT / 64), "one y window per thread");
   __shared__ T s_in[H][W];
@@ -315,10 +415,13 @@ __global__ __launch_bounds__(512) void blur_xy(const T* __restrict__ in, T* __re
   // Tiles in the hardware's order: this pass is bound by its LDS and VALU
   // work, not by its halo fetches (those hit MALL), and xcd_tile's placement
   // measured slower for it (16 x 100^3: 656 against 648 us per iteration).
-  const int z = blockIdx.z % d.nz, b = blockIdx.z / d.nz;
+  // with a box, rows, planes and x count from its corner
+  const int nx = EDGE == kPeriodic ? d.nx : e.nx, ny = EDGE == kPeriodic ? d.ny : e.ny;
+  const int z = EDGE == kPeriodic ? blockIdx.z % d.nz : e.lo + blockIdx.z;
+  const int b = EDGE == kPeriodic ? blockIdx.z / d.nz : 0;
   const int x0 = ROWS ? 0 : blockIdx.x * 64, y0 = blockIdx.y * kXYRows;
   const size_t plane = (size_t)d.nx * d.ny, vol = plane * d.nz;
-  const T* src = in + (size_t)b * vol + (size_t)z * plane;
+  const T* src = in + (size_t)b * vol + (size_t)z * plane + (EDGE == kPeriodic ? 0 : (size_t)e.lo * d.nx + e.lo);
   // Stage the tile with its halo: wave w takes the rows w, w + 8, ... (their y
   // is wave-uniform, so it lives in scalar registers), lane l the columns l
   // and, for l < 2R, 64 + l. All loads of a thread are issued before the
@@ -326,16 +429,46 @@ __global__ __launch_bounds__(512) void blur_xy(const T* __restrict__ in, T* __re
   constexpr int RPW = (H + NT / 64 - 1) / (NT / 64);   // rows per wave
   const int wy = __builtin_amdgcn_readfirstlane(threadIdx.y);
   const int lane = threadIdx.x;
-  const int xc0 = wrap_any(x0 - R + lane, d.nx), xc1 = wrap_any(x0 - R + 64 + lane, d.nx);
-  const bool second = ROWS ? 64 + lane < d.nx + 2 * R : lane < 2 * R;
+  auto index = [](int v, int n) {
+    return EDGE == kPeriodic ? wrap_any(v, n) : EDGE == kReplicate ? clamp_index(v, n) : v;
+  };
+  const int xc0 = index(x0 - R + lane, nx), xc1 = index(x0 - R + 64 + lane, nx);
+  const bool second = ROWS ? 64 + lane < nx + 2 * R : lane < 2 * R + X1;
   T v[RPW][2];
 #pragma unroll
   for (int i = 0; i < RPW; ++i) {
     const int rr = wy + (NT / 64) * i;
     if (rr >= H) continue;
-    const T* row = src + (size_t)wrap_any(y0 - R + rr, d.ny) * d.nx;
-    v[i][0] = row[xc0];
-    if (second) v[i][1] = row[xc1];
+    const int y = index(y0 - R + rr, ny);
+    if constexpr (EDGE == kAdjoint) {
+      // the box's rows with the samples beyond their ends; zeros elsewhere
+      const T* row = src + (size_t)y * d.nx;
+      const bool yin = y >= 0 && y < ny;
+      v[i][0] = yin && xc0 >= -1 && xc0 <= nx ? row[xc0] : T(0);
+      if (second) v[i][1] = yin && xc1 >= -1 && xc1 <= nx ? row[xc1] : T(0);
+    } else {
+      const T* row = src + (size_t)y * d.nx;
+      v[i][0] = row[xc0];
+      if (second) v[i][1] = row[xc1];
+    }
+  }
+  if constexpr (EDGE == kAdjoint) {
+    // Fold what the sweep left outside the box onto its faces: in z and y here, for
+    // the few rows that are faces (uniform per wave), in x between staged columns.
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      const int rr = wy + (NT / 64) * i;
+      if (rr >= H) continue;
+      const int y = y0 - R + rr, zb = z - e.lo;
+      if (y < 0 || y >= ny) continue;
+      for (int kz = zb == 0 ? -1 : 0; kz <= (zb == e.nz - 1 ? 1 : 0); ++kz)
+        for (int ky = y == 0 ? -1 : 0; ky <= (y == ny - 1 ? 1 : 0); ++ky) {
+          if (kz == 0 && ky == 0) continue;
+          const T* row = src + (long)kz * (long)plane + (long)(y + ky) * d.nx;
+          if (xc0 >= -1 && xc0 <= nx) v[i][0] += row[xc0];
+          if (second && xc1 >= -1 && xc1 <= nx) v[i][1] += row[xc1];
+        }
+    }
   }
 #pragma unroll
   for (int i = 0; i < RPW; ++i) {
@@ -345,10 +478,27 @@ __global__ __launch_bounds__(512) void blur_xy(const T* __restrict__ in, T* __re
     if (second) s_in[rr][64 + lane] = v[i][1];
   }
   __syncthreads();
+  if constexpr (EDGE == kAdjoint) {
+    const int lo = R - x0, hi = nx - 1 + R - x0;        // the faces' staged columns
+    const bool far = hi + 1 < (ROWS ? kRowsMax : W);
+    if (x0 == 0 || far) {
+      for (int rr = tid; rr < H; rr += NT) {
+        if (x0 == 0) {
+          s_in[rr][lo] += s_in[rr][lo - 1];
+          s_in[rr][lo - 1] = T(0);
+        }
+        if (far) {
+          s_in[rr][hi] += s_in[rr][hi + 1];
+          s_in[rr][hi + 1] = T(0);
+        }
+      }
+      __syncthreads();
+    }
+  }
   // x blur of every staged row: thread -> (row, quad of four x-values); QPR
   // quads per row (ROWS: the row's ceil(nx/4) of 32 slots)
   constexpr int QPR = ROWS ? 32 : 16;
-  const int nquad = ROWS ? (d.nx + OUT - 1) / OUT : 16;
+  const int nquad = ROWS ? (nx + OUT - 1) / OUT : 16;
 #pragma unroll
   for (int p = 0; p < (H * QPR + NT - 1) / NT; ++p) {
     const int q = tid % QPR, rr = tid / QPR + p * (NT / QPR);
@@ -361,6 +511,10 @@ __global__ __launch_bounds__(512) void blur_xy(const T* __restrict__ in, T* __re
         T acc = T(0);
 #pragma unroll
         for (int j = 0; j <= 2 * R; ++j) acc += k.w[j] * w[o + j];
+        if (EDGE == kAdjoint) {
+          const int x = x0 + 4 * q + o;
+          if (x == 0 || x == nx - 1) acc = face_dot<T, R>(k, w + o + R, x == 0, x == nx - 1);
+        }
         s_mid[rr][4 * q + o] = acc;
       }
     }
@@ -371,18 +525,23 @@ __global__ __launch_bounds__(512) void blur_xy(const T* __restrict__ in, T* __re
   for (int jx = 0; jx < (ROWS ? 2 : 1); ++jx) {
     const int xo = threadIdx.x + 64 * jx;
     const int x = x0 + xo;
-    if (x >= d.nx) break;
+    if (x >= nx) break;
     T col[OUT + 2 * R];
 #pragma unroll
     for (int i = 0; i < OUT + 2 * R; ++i) col[i] = s_mid[threadIdx.y * OUT + i][xo];
 #pragma unroll
     for (int o = 0; o < OUT; ++o) {
       const int y = y0 + threadIdx.y * OUT + o;
-      if (y >= d.ny) break;
+      if (y >= ny) break;
       T acc = T(0);
 #pragma unroll
       for (int j = 0; j <= 2 * R; ++j) acc += k.w[j] * col[o + j];
-      out[(size_t)b * vol + (size_t)z * plane + (size_t)y * d.nx + x] = acc;
+      if (EDGE == kPeriodic) {
+        out[(size_t)b * vol + (size_t)z * plane + (size_t)y * d.nx + x] = acc;
+      } else {
+        if (EDGE == kAdjoint && (y == 0 || y == ny - 1)) acc = face_dot<T, R>(k, col + o + R, y == 0, y == ny - 1);
+        out[e.ooff + (size_t)blockIdx.z * e.oplane + (size_t)y * e.orow + x] = acc;
+      }
     }
   }
 }

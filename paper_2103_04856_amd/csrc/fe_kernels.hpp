@@ -370,9 +370,10 @@ __device__ __forceinline__ BlockTile block_tile(const SweepArgs<T>& a) {
 // SP: the coefficients C1..C6 come per voxel from a.cfield (loaded for every
 // ring voxel of a plane right after the plane is staged, so their latency
 // overlaps the barrier) instead of from the instance's parameters.
-// BOX: only voxels inside [box_lo, box_hi) carry a density; the others (the
-// padding of a non-periodic field) have zero adjoints, and the gradient is
-// written at every voxel, padding included, for the caller to fold back.
+// BOX: only voxels inside [box_lo, box_hi) carry a density, and samples outside are
+// read as the nearest ones in the box; the voxels outside have zero adjoints, and
+// the gradient is written at every voxel, those outside included, for the caller
+// to fold back.
 // EN: the energy of the swept field is wanted. Without it (the gradient of a
 // backward pass, every step or flow iteration whose energy nobody reads) the
 // density is not formed and partial [0] is 0.
@@ -480,13 +481,17 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad
   // thread's output voxels, computed once. A plane is under 4 GiB (checked on the
   // host), so every load and store is a block-uniform plane address plus a 32-bit
   // lane offset, with no 64-bit address arithmetic per access.
+  // The sample at index v of an axis: periodic, or (BOX) the nearest in the box.
+  auto axis_index = [&](int v, int n, int ax) {
+    return BOX ? min(max(v, a.box_lo[ax]), a.box_hi[ax] - 1) : wrap_index(v, n);
+  };
   unsigned uoff[NU];
 #pragma unroll
   for (int j = 0; j < NU; ++j) {
     const int e = tid + j * NT;
     const int ex = e % UX, ey = e / UX;
     uoff[j] = (e < UX * UY)
-                  ? (unsigned)(wrap_index(y0 - 2 + ey, a.ny) * a.nx + wrap_index(x0 - 2 + ex, a.nx)) * sizeof(T)
+                  ? (unsigned)(axis_index(y0 - 2 + ey, a.ny, 1) * a.nx + axis_index(x0 - 2 + ex, a.nx, 0)) * sizeof(T)
                   : 0u;
   }
   // this thread's output voxel j: whether it has one, its tile column and row, its ring position
@@ -517,7 +522,7 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad
     for (int j = 0; j < NU; ++j)
       if (tid + j * NT < UX * UY) pre[j] = buffer_load(r, uoff[j], T());
   };
-  auto fetch = [&](int p) { fetch_wrapped(wrap_index(p, a.nz)); };
+  auto fetch = [&](int p) { fetch_wrapped(axis_index(p, a.nz, 2)); };
   auto stage = [&](int slot) {
 #pragma unroll
     for (int j = 0; j < NU; ++j) {
@@ -644,14 +649,14 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad
 
   const int nit = (kend - k0) + 2;             // forward planes k0-1 .. kend
   int sm = 0, sc = 1, sp = 2;                  // slots of p-1, p, p+1
-  int pf = wrap_index(k0 + 1, a.nz);           // plane p + 2, wrapped (advanced by one per plane)
+  int pf = axis_index(k0 + 1, a.nz, 2);        // plane p + 2, wrapped (advanced by one per plane)
   start_priority();
   for (int it = 0; it < nit; ++it) {
     const int p = k0 - 1 + it;
     progress_priority(it, nit);
     stage(sp);
     if (it + 1 < nit) fetch_wrapped(pf);       // plane p + 2, in flight during this plane's compute
-    pf = pf + 1 == a.nz ? 0 : pf + 1;
+    pf = BOX ? axis_index(p + 3, a.nz, 2) : pf + 1 == a.nz ? 0 : pf + 1;
     // Adam moments of output plane p (written in the next iteration), loaded a
     // whole plane ahead: the wait for them then leaves this plane's stores in
     // flight (loads and stores share one in-order counter)

@@ -1,16 +1,20 @@
 // Device pieces of Algorithm 2 (Sec. 4.2): the L2 flow of F_h(k * u) with
 // replicate boundary conditions, driven by L-BFGS.
 //
-// The box field lives inside a padded array (pad width W on every side); the
-// padding holds copies of the nearest box voxel (replicate padding) whenever a
-// stencil or the blur reads it. The sweep then runs on the padded array as a
-// periodic field with a box mask, and the derivatives that land on pad samples
-// are added back onto the box voxels they copy (the transpose of the padding).
-// Vectors of the optimiser use the same padded layout with zero padding.
+// The box field lives inside an array with one more sample on every side. The blur
+// and the sweep read the nearest box voxel wherever they would read outside the
+// box (BlurEdge kReplicate; the sweep's BOX form), so the margin holds no copies:
+// it takes the derivatives that the sweep's stencils leave one sample outside the
+// box, which are then added back onto the voxels those samples copy (folded), and
+// is zero in the optimiser's vectors, which share the layout. A margin as wide as
+// the blur, filled before it and folded after it, took seven more passes per
+// evaluation and 13 % longer vectors at 192^3 and sigma_k = 1 (192^3 FP32 energy
+// and gradient 287 -> 171 us per call).
 #pragma once
 
 #include <hip/hip_runtime.h>
 
+#include "fe_flow.hpp"
 #include "fe_kernels.hpp"
 
 namespace fe {
@@ -20,140 +24,16 @@ struct PadBox {
   int lo[3], hi[3];        // box [lo, hi) in x, y, z
 };
 
-__device__ __forceinline__ int clamp_to(int v, int lo, int hi) { return v < lo ? lo : (v >= hi ? hi - 1 : v); }
-
-// Fill every pad sample with the nearest box voxel (reads box voxels only).
-// Threads enumerate the pad shell alone, in three regions: the planes below
-// and above the box in z, then within the box's z range the rows below and
-// above it in y, then within the box's y and z ranges the runs left and right
-// of it in x. Grid: ceil(shell / 256) blocks of 256 (pad_shell_size).
-__host__ __device__ __forceinline__ size_t pad_shell_size(const PadBox& b) {
-  const size_t bx = b.hi[0] - b.lo[0], by = b.hi[1] - b.lo[1], bz = b.hi[2] - b.lo[2];
-  const size_t px = b.nx - bx, py = b.ny - by, pz = b.nz - bz;
-  return pz * b.ny * b.nx + bz * py * b.nx + bz * by * px;
-}
-
+// out = folded(g) at every box voxel: the gradient without a blur. Grid
+// (ceil(nx ny / 256), nz) over the box.
 template <typename T>
-__global__ __launch_bounds__(256) void pad_replicate(T* __restrict__ f, PadBox b) {
-  const size_t bx = b.hi[0] - b.lo[0], by = b.hi[1] - b.lo[1], bz = b.hi[2] - b.lo[2];
-  const size_t px = b.nx - bx, py = b.ny - by, pz = b.nz - bz;
-  const size_t nA = pz * b.ny * b.nx, nB = bz * py * b.nx, nC = bz * by * px;
-  size_t j = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int x, y, z;
-  if (j < nA) {
-    const size_t plane = (size_t)b.nx * b.ny;
-    const int k = (int)(j / plane), r = (int)(j % plane);
-    z = k < b.lo[2] ? k : b.hi[2] + (k - b.lo[2]);
-    y = r / b.nx;
-    x = r % b.nx;
-  } else if ((j -= nA) < nB) {
-    const size_t per = py * b.nx;
-    const int k = (int)(j / per), r = (int)(j % per);
-    const int ky = r / b.nx;
-    z = b.lo[2] + k;
-    y = ky < b.lo[1] ? ky : b.hi[1] + (ky - b.lo[1]);
-    x = r % b.nx;
-  } else if ((j -= nB) < nC) {
-    const int row = (int)(j / px), kx = (int)(j % px);
-    z = b.lo[2] + row / (int)by;
-    y = b.lo[1] + row % (int)by;
-    x = kx < b.lo[0] ? kx : b.hi[0] + (kx - b.lo[0]);
-  } else {
-    return;
-  }
-  const int cx = clamp_to(x, b.lo[0], b.hi[0]), cy = clamp_to(y, b.lo[1], b.hi[1]), cz = clamp_to(z, b.lo[2], b.hi[2]);
-  f[((size_t)z * b.ny + y) * b.nx + x] = f[((size_t)cz * b.ny + cy) * b.nx + cx];
-}
-
-// out = P^T g: every box voxel gathers the pad samples that copy it (on a box
-// face, the run of pad samples beyond it along each clamped axis, the voxel
-// included); pad samples of out are zero; voxels off the box surface copy g.
-// W > 0: every pad is W wide and the box is at least 2 voxels along every
-// axis, so a run on one face is W + 1 samples at fixed offsets and an edge or a
-// corner gathers (W+1)^2 or (W+1)^3 of them (unrolled, loads in flight);
-// W = 0: general runs, for any box (a box 1 voxel thick has runs on both of
-// its sides). One thread per sample of a plane: grid (ceil(nx ny / 256), nz).
-// g and out must differ.
-template <typename T, int W>
-__global__ __launch_bounds__(256) void fold_pads(const T* __restrict__ g, T* __restrict__ out, PadBox b) {
-  const int ip = blockIdx.x * 256 + threadIdx.x, z = blockIdx.y;
-  if (ip >= b.nx * b.ny) return;
-  const int y = ip / b.nx, x = ip - y * b.nx;
-  const size_t i = (size_t)z * b.nx * b.ny + ip;
-  const bool in = x >= b.lo[0] && x < b.hi[0] && y >= b.lo[1] && y < b.hi[1] && z >= b.lo[2] && z < b.hi[2];
-  if (!in) {
-    out[i] = T(0);
-    return;
-  }
-  const bool fx = x == b.lo[0] || x == b.hi[0] - 1, fy = y == b.lo[1] || y == b.hi[1] - 1,
-             fz = z == b.lo[2] || z == b.hi[2] - 1;
-  const int nf = int(fx) + int(fy) + int(fz);
-  if (nf == 0) {
-    out[i] = g[i];
-    return;
-  }
-  if (W > 0 && nf == 1) {
-    // the run from the voxel outwards along its one clamped axis
-    const int lo = fx ? b.lo[0] : fy ? b.lo[1] : b.lo[2];
-    const int c = fx ? x : fy ? y : z;
-    const long step = fx ? 1 : fy ? (long)b.nx : (long)b.nx * b.ny;
-    const long dir = c == lo ? -step : step;
-    T v[W + 1];
-#pragma unroll
-    for (int k = 0; k <= W; ++k) v[k] = g[(long)i + k * dir];
-    T acc = T(0);                // in increasing index order, as the general loop adds
-    if (dir < 0) {
-#pragma unroll
-      for (int k = W; k >= 0; --k) acc += v[k];
-    } else {
-#pragma unroll
-      for (int k = 0; k <= W; ++k) acc += v[k];
-    }
-    out[i] = acc;
-    return;
-  }
-  const int x0 = x == b.lo[0] ? 0 : x, x1 = x == b.hi[0] - 1 ? b.nx - 1 : x;
-  const int y0 = y == b.lo[1] ? 0 : y, y1 = y == b.hi[1] - 1 ? b.ny - 1 : y;
-  const int z0 = z == b.lo[2] ? 0 : z, z1 = z == b.hi[2] - 1 ? b.nz - 1 : z;
-  if (W > 0) {
-    // An edge or a corner: the (W+1)^2 block spanned by the runs along two
-    // clamped axes, every load in flight. On an edge the third axis is fixed;
-    // on a corner the block is in (y, x) and z runs over its W + 1 planes.
-    // Blocks are summed in increasing index order, as the general loop adds.
-    const long sx = 1, sy = b.nx, sz = (long)b.nx * b.ny;
-    long sp = sy, sq = sx, so = sz;
-    int no = fz ? W + 1 : 1;
-    if (nf == 2 && fz) {
-      no = 1;
-      if (!fy) {
-        sp = sz;
-        sq = sx;
-        so = sy;
-      } else {
-        sp = sz;
-        sq = sy;
-        so = sx;
-      }
-    }
-    const T* p0 = g + ((size_t)z0 * b.ny + y0) * b.nx + x0;
-    T acc = T(0);
-    for (int ko = 0; ko < no; ++ko) {
-      T v[(W + 1) * (W + 1)];
-#pragma unroll
-      for (int kp = 0; kp <= W; ++kp)
-#pragma unroll
-        for (int kq = 0; kq <= W; ++kq) v[kp * (W + 1) + kq] = p0[ko * so + kp * sp + kq * sq];
-#pragma unroll
-      for (int k = 0; k < (W + 1) * (W + 1); ++k) acc += v[k];
-    }
-    out[i] = acc;
-    return;
-  }
-  T acc = T(0);
-  for (int zz = z0; zz <= z1; ++zz)
-    for (int yy = y0; yy <= y1; ++yy)
-      for (int xx = x0; xx <= x1; ++xx) acc += g[((size_t)zz * b.ny + yy) * b.nx + xx];
-  out[i] = acc;
+__global__ __launch_bounds__(256) void fold_shell(const T* __restrict__ g, T* __restrict__ out, FieldDims d,
+                                                  EdgeBox e) {
+  const unsigned q = blockIdx.x * 256u + threadIdx.x;
+  if (q >= (unsigned)e.nx * (unsigned)e.ny) return;
+  const unsigned y = q / (unsigned)e.nx, x = q - y * (unsigned)e.nx;
+  out[e.ooff + (size_t)blockIdx.y * e.oplane + (size_t)y * e.orow + x] =
+      folded(g, d, e, (int)x, (int)y, e.lo + (int)blockIdx.y);
 }
 
 // ---- vector operations of the optimiser (FP64 reductions, fixed order) ----
@@ -454,17 +334,29 @@ __global__ __launch_bounds__(64) void vec_finish(BankList l) {
   }
 }
 
-// Copy between the box of a padded array and a dense box field [nz][ny][nx].
+// Copy between the box of a padded array and a dense box field [nz][ny][nx]: four
+// voxels of a plane per thread, 256 apart, all loaded before the first is stored.
+// Grid (ceil(nx ny / 1024), nz) over the box.
 template <typename T>
 __global__ __launch_bounds__(256) void box_copy(const T* __restrict__ src, T* __restrict__ dst, PadBox b,
                                                 int to_padded) {
-  const int bx = b.hi[0] - b.lo[0], by = b.hi[1] - b.lo[1], bz = b.hi[2] - b.lo[2];
-  const size_t n = (size_t)bx * by * bz;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int x = (int)(i % bx), y = (int)((i / bx) % by), z = (int)(i / ((size_t)bx * by));
-    const size_t pi = ((size_t)(z + b.lo[2]) * b.ny + (y + b.lo[1])) * b.nx + (x + b.lo[0]);
-    if (to_padded) dst[pi] = src[i];
-    else dst[i] = src[pi];
+  constexpr int U = 4;
+  const unsigned bx = b.hi[0] - b.lo[0], by = b.hi[1] - b.lo[1], n = bx * by;
+  const size_t dz = (size_t)blockIdx.y * n;
+  const size_t pz = ((size_t)(blockIdx.y + b.lo[2]) * b.ny + b.lo[1]) * b.nx + b.lo[0];
+  const unsigned q0 = blockIdx.x * (256u * U) + threadIdx.x;
+  T v[U];
+  size_t p[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const unsigned q = q0 + 256u * u, y = q / bx;
+    p[u] = pz + (size_t)y * b.nx + (q - y * bx);
+    if (q < n) v[u] = to_padded ? src[dz + q] : src[p[u]];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const unsigned q = q0 + 256u * u;
+    if (q < n) dst[to_padded ? p[u] : dz + q] = v[u];
   }
 }
 

@@ -15,6 +15,11 @@ fe::BlurTaps<T> blur_taps(double sigma_k) {
     sum += w[j + k.r];
   }
   for (int j = 0; j <= 2 * k.r; ++j) k.w[j] = T(w[j] / sum);
+  double c = 0.0;
+  for (int j = k.r; j >= 0; --j) {
+    c += w[k.r + j] / sum;
+    k.c[j] = T(c);
+  }
   return k;
 }
 
@@ -22,11 +27,12 @@ struct FlowRule {
   double sigma_k, lr, beta1, beta2, adam_eps;
 };
 
-// Launch shapes of the flow kernels.
-dim3 x_grid(const fe::FieldDims& d) { return dim3(ceil_div(d.nx, 64), ceil_div(d.ny, fe::kBlurRows), d.nz * d.batch); }
-dim3 axis_grid(const fe::FieldDims& d, int axis) {
-  return axis == 1 ? dim3(ceil_div(d.nz * d.nx, 256), ceil_div(d.ny, fe::kAxisChunk), d.batch)
-                   : dim3(ceil_div(d.nx * d.ny, 256), ceil_div(d.nz, fe::kAxisChunk), d.batch);
+// Launch shapes of the flow kernels; the blur passes over n = (nx, ny, nz) voxels,
+// the field's or a box's.
+dim3 x_grid(const fe::FieldDims& n) { return dim3(ceil_div(n.nx, 64), ceil_div(n.ny, fe::kBlurRows), n.nz * n.batch); }
+dim3 axis_grid(const fe::FieldDims& n, int axis) {
+  return axis == 1 ? dim3(ceil_div(n.nz * n.nx, 256), ceil_div(n.ny, fe::kAxisChunk), n.batch)
+                   : dim3(ceil_div(n.nx * n.ny, 256), ceil_div(n.nz, fe::kAxisChunk), n.batch);
 }
 // The flow kernels address a plane with 32-bit byte offsets and number the
 // columns of the y pass (nz * nx of them) in 32-bit integers.
@@ -41,54 +47,71 @@ dim3 plane_grid(const fe::FieldDims& d) { return dim3(ceil_div(d.nx * d.ny, 256)
 // the 128 staged values.
 bool rows_fit(const fe::FieldDims& d, int r) { return d.nx + 2 * r <= fe::kRowsMax; }
 
+// The voxels a pass covers: the box's unless it is periodic.
+template <int EDGE>
+fe::FieldDims pass_dims(const fe::FieldDims& d, const fe::EdgeBox& e) {
+  return EDGE == fe::kPeriodic ? d : fe::FieldDims{e.nx, e.ny, e.nz, 1};
+}
+
 // The x pass (with the divergence when DIV), dispatched to the fixed-radius
 // instantiation when there is one, and to its ROWS form when the rows fit.
-template <typename T, bool DIV>
+template <typename T, bool DIV, int EDGE = fe::kPeriodic>
 void blur_x_pass(hipStream_t s, const fe::FieldDims& d, const fe::BlurTaps<T>& k, const T* in, T* out,
-                 const double* m0, const T* mfield, T inv2h, fe::FlowClock* clk, double beta1, double beta2) {
-  const dim3 g = x_grid(d), b(64, 4);
+                 const double* m0, const T* mfield, T inv2h, fe::FlowClock* clk, double beta1, double beta2,
+                 const fe::EdgeBox& e = {}) {
+  const fe::FieldDims n = pass_dims<EDGE>(d, e);
+  const dim3 g = x_grid(n), b(64, 4);
   const dim3 gr(1, g.y, g.z);
-  if (k.r == 4 && rows_fit(d, 4))
-    hipLaunchKernelGGL((fe::blur_x<T, DIV, 4, true>), gr, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1,
-                       beta2);
-  else if (k.r == 8 && rows_fit(d, 8))
-    hipLaunchKernelGGL((fe::blur_x<T, DIV, 8, true>), gr, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1,
-                       beta2);
-  else if (k.r == 4)
-    hipLaunchKernelGGL((fe::blur_x<T, DIV, 4>), g, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1, beta2);
-  else if (k.r == 8)
-    hipLaunchKernelGGL((fe::blur_x<T, DIV, 8>), g, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1, beta2);
-  else
-    hipLaunchKernelGGL((fe::blur_x<T, DIV>), g, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1, beta2);
+  if constexpr (EDGE == fe::kPeriodic) {
+    if (k.r == 4 && rows_fit(n, 4))
+      hipLaunchKernelGGL((fe::blur_x<T, DIV, 4, true>), gr, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1,
+                         beta2, e);
+    else if (k.r == 8 && rows_fit(n, 8))
+      hipLaunchKernelGGL((fe::blur_x<T, DIV, 8, true>), gr, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1,
+                         beta2, e);
+    else if (k.r == 4)
+      hipLaunchKernelGGL((fe::blur_x<T, DIV, 4>), g, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1, beta2, e);
+    else if (k.r == 8)
+      hipLaunchKernelGGL((fe::blur_x<T, DIV, 8>), g, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1, beta2, e);
+    else
+      hipLaunchKernelGGL((fe::blur_x<T, DIV>), g, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1, beta2, e);
+  } else {
+    // with a box this pass serves the radii without an x-y pass only
+    hipLaunchKernelGGL((fe::blur_x<T, DIV, -1, false, EDGE>), g, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1,
+                       beta2, e);
+  }
 }
 
 // The fused x-then-y pass, for the radii that have one (r = 4 and 8).
 bool has_xy_pass(int r) { return r == 4 || r == 8; }
-dim3 xy_grid(const fe::FieldDims& d) { return dim3(ceil_div(d.nx, 64), ceil_div(d.ny, fe::kXYRows), d.nz * d.batch); }
+dim3 xy_grid(const fe::FieldDims& n) { return dim3(ceil_div(n.nx, 64), ceil_div(n.ny, fe::kXYRows), n.nz * n.batch); }
 
-template <typename T>
-void blur_xy_pass(hipStream_t s, const fe::FieldDims& d, const fe::BlurTaps<T>& k, const T* in, T* out) {
-  const dim3 g = xy_grid(d), b(64, 8);
+template <typename T, int EDGE = fe::kPeriodic>
+void blur_xy_pass(hipStream_t s, const fe::FieldDims& d, const fe::BlurTaps<T>& k, const T* in, T* out,
+                  const fe::EdgeBox& e = {}) {
+  const fe::FieldDims n = pass_dims<EDGE>(d, e);
+  const dim3 g = xy_grid(n), b(64, 8);
   const dim3 gr(1, g.y, g.z);
-  if (k.r == 4 && rows_fit(d, 4))
-    hipLaunchKernelGGL((fe::blur_xy<T, 4, true>), gr, b, 0, s, in, out, d, k);
+  if (k.r == 4 && rows_fit(n, 4))
+    hipLaunchKernelGGL((fe::blur_xy<T, 4, true, EDGE>), gr, b, 0, s, in, out, d, k, e);
   else if (k.r == 4)
-    hipLaunchKernelGGL((fe::blur_xy<T, 4>), g, b, 0, s, in, out, d, k);
-  else if (rows_fit(d, 8))
-    hipLaunchKernelGGL((fe::blur_xy<T, 8, true>), gr, b, 0, s, in, out, d, k);
+    hipLaunchKernelGGL((fe::blur_xy<T, 4, false, EDGE>), g, b, 0, s, in, out, d, k, e);
+  else if (rows_fit(n, 8))
+    hipLaunchKernelGGL((fe::blur_xy<T, 8, true, EDGE>), gr, b, 0, s, in, out, d, k, e);
   else
-    hipLaunchKernelGGL((fe::blur_xy<T, 8>), g, b, 0, s, in, out, d, k);
+    hipLaunchKernelGGL((fe::blur_xy<T, 8, false, EDGE>), g, b, 0, s, in, out, d, k, e);
 }
 
-template <typename T, int AXIS>
-void blur_axis_pass(hipStream_t s, const fe::FieldDims& d, const fe::BlurTaps<T>& k, const T* in, T* out) {
-  const dim3 g = axis_grid(d, AXIS), b(256);
+template <typename T, int AXIS, int EDGE = fe::kPeriodic>
+void blur_axis_pass(hipStream_t s, const fe::FieldDims& d, const fe::BlurTaps<T>& k, const T* in, T* out,
+                    const fe::EdgeBox& e = {}) {
+  const dim3 g = axis_grid(pass_dims<EDGE>(d, e), AXIS), b(256);
   if (k.r == 4)
-    hipLaunchKernelGGL((fe::blur_axis<T, AXIS, 4>), g, b, 0, s, in, out, d, k);
+    hipLaunchKernelGGL((fe::blur_axis<T, AXIS, 4, EDGE>), g, b, 0, s, in, out, d, k, e);
   else if (k.r == 8)
-    hipLaunchKernelGGL((fe::blur_axis<T, AXIS, 8>), g, b, 0, s, in, out, d, k);
+    hipLaunchKernelGGL((fe::blur_axis<T, AXIS, 8, EDGE>), g, b, 0, s, in, out, d, k, e);
   else
-    hipLaunchKernelGGL((fe::blur_axis<T, AXIS>), g, b, 0, s, in, out, d, k);
+    hipLaunchKernelGGL((fe::blur_axis<T, AXIS, -1, EDGE>), g, b, 0, s, in, out, d, k, e);
 }
 
 // out = k * f along y then z, through `tmp` (f is left as it was; out may be f).

@@ -35,7 +35,21 @@ struct fe_l2 {
 
 namespace {
 
-int l2_launch_1d(size_t n) { return (int)std::min<size_t>((n + 255) / 256, 65536); }
+// Copies between the box of the flow's array and a dense box field.
+template <typename T>
+int l2_box_copy(fe_l2* L, const void* src, void* dst, int to_padded) {
+  const fe::PadBox& b = L->box;
+  const int bx = b.hi[0] - b.lo[0], by = b.hi[1] - b.lo[1], bz = b.hi[2] - b.lo[2];
+  hipLaunchKernelGGL(fe::box_copy<T>, dim3((unsigned)ceil_div(bx * by, 1024), (unsigned)bz), dim3(256), 0,
+                     L->ctx->stream, static_cast<const T*>(src), static_cast<T*>(dst), b, to_padded);
+  FE_HIP(hipGetLastError());
+  return FE_OK;
+}
+
+int l2_box_copy_any(fe_l2* L, const void* src, void* dst, int to_padded) {
+  return L->ctx->grid.dtype == FE_F32 ? l2_box_copy<float>(L, src, dst, to_padded)
+                                      : l2_box_copy<double>(L, src, dst, to_padded);
+}
 
 // Scalars of the optimiser. Named slots: 0 energy, 1 max|g|, 2 max|d|, 3 g'd
 // and 4 |g|_1 (first iteration); then the inner products of the Gram pass
@@ -197,85 +211,80 @@ int l2_gram(fe_l2* L, const std::vector<const void*>& hist, std::vector<double>&
   return FE_OK;
 }
 
-// The separable blur passes on the padded array (periodic within it):
-// in -> tmp1 (x) -> tmp2 (y) -> out (z), or in -> tmp1 (fused x-y) -> out (z)
-// for r = 4, 8; in and out may coincide, tmp1/tmp2 not.
-template <typename T>
-void l2_blur(fe_l2* L, const T* in, T* tmp1, T* tmp2, T* out) {
+// The box of the flow's arrays; a pass with this writes box voxels in place.
+fe::EdgeBox l2_edge(const fe_l2* L) {
+  const fe::PadBox& b = L->box;
+  const size_t row = b.nx, plane = (size_t)b.nx * b.ny;
+  return fe::EdgeBox{b.lo[0], b.hi[0] - b.lo[0], b.hi[1] - b.lo[1], b.hi[2] - b.lo[2],
+                     row,     plane,             b.lo[2] * plane + b.lo[1] * row + b.lo[0]};
+}
+
+// The same box, written as a dense box field.
+fe::EdgeBox l2_dense(const fe_l2* L) {
+  fe::EdgeBox e = l2_edge(L);
+  e.orow = e.nx;
+  e.oplane = (size_t)e.nx * e.ny;
+  e.ooff = 0;
+  return e;
+}
+
+// The separable blur of the box (EDGE: fe::kReplicate forward, fe::kAdjoint with the
+// fold of the sweep's gradient): in -> tmp1 (x) -> tmp2 (y) -> out (z), or
+// in -> tmp1 (fused x-y) -> out (z) for r = 4, 8; tmp1 and tmp2 in the array's
+// layout, out as `eo` says; out may be in.
+template <typename T, int EDGE>
+void l2_blur(fe_l2* L, const T* in, T* tmp1, T* tmp2, T* out, const fe::EdgeBox& eo) {
   const fe::FieldDims d{L->box.nx, L->box.ny, L->box.nz, 1};
   const fe::BlurTaps<T> k = blur_taps<T>(L->sigma_k);
+  const fe::EdgeBox e = l2_edge(L);
   hipStream_t s = L->ctx->stream;
   if (has_xy_pass(k.r)) {
-    blur_xy_pass<T>(s, d, k, in, tmp1);
-    blur_axis_pass<T, 2>(s, d, k, tmp1, out);
+    blur_xy_pass<T, EDGE>(s, d, k, in, tmp1, e);
+    blur_axis_pass<T, 2, EDGE>(s, d, k, tmp1, out, eo);
     return;
   }
-  blur_x_pass<T, false>(s, d, k, in, tmp1, nullptr, nullptr, T(0), nullptr, 0.0, 0.0);
-  blur_yz<T>(s, d, k, tmp1, tmp2, out);
+  blur_x_pass<T, false, EDGE>(s, d, k, in, tmp1, nullptr, nullptr, T(0), nullptr, 0.0, 0.0, e);
+  blur_axis_pass<T, 1, EDGE>(s, d, k, tmp1, tmp2, e);
+  blur_axis_pass<T, 2, EDGE>(s, d, k, tmp2, out, eo);
 }
 
-// The padding kernels: replicate padding over the pad shell, and its
-// transpose (fixed-width runs for the pad widths 1, 4 and 8 on boxes at least
-// 2 voxels thick, general runs otherwise).
+// F_h(k * x) with replicate boundaries into the energy slot and its gradient into
+// g, which takes box voxels only, laid out as `eo` says; stream-ordered.
 template <typename T>
-void l2_pad(fe_l2* L, T* f) {
-  const size_t n = fe::pad_shell_size(L->box);
-  if (n == 0) return;
-  hipLaunchKernelGGL(fe::pad_replicate<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, L->ctx->stream, f,
-                     L->box);
-}
-
-template <typename T>
-void l2_fold(fe_l2* L, const T* g, T* out) {
-  const dim3 grid((unsigned)ceil_div(L->box.nx * L->box.ny, 256), (unsigned)L->box.nz);
-  hipStream_t s = L->ctx->stream;
-  // the fixed-width forms need a box at least 2 voxels thick on every axis
-  bool thick = true;
-  for (int a = 0; a < 3; ++a) thick = thick && L->box.hi[a] - L->box.lo[a] >= 2;
-  const int W = thick ? L->box.lo[0] : 0;
-  if (W == 4)
-    hipLaunchKernelGGL((fe::fold_pads<T, 4>), grid, dim3(256), 0, s, g, out, L->box);
-  else if (W == 8)
-    hipLaunchKernelGGL((fe::fold_pads<T, 8>), grid, dim3(256), 0, s, g, out, L->box);
-  else if (W == 1)
-    hipLaunchKernelGGL((fe::fold_pads<T, 1>), grid, dim3(256), 0, s, g, out, L->box);
-  else
-    hipLaunchKernelGGL((fe::fold_pads<T, 0>), grid, dim3(256), 0, s, g, out, L->box);
-}
-
-// F_h(k * x) with replicate boundaries into the energy slot and g = its
-// gradient (zero padding), stream-ordered.
-template <typename T>
-int l2_eval_dev(fe_l2* L) {
+int l2_eval_dev(fe_l2* L, T* g, const fe::EdgeBox& eo) {
   T* x = static_cast<T*>(L->x);
-  T* g = static_cast<T*>(L->g);
   T* w0 = static_cast<T*>(L->w0);
   T* w1 = static_cast<T*>(L->w1);
   T* w2 = static_cast<T*>(L->w2);
-  l2_pad<T>(L, x);
   const T* ub = x;
   if (L->r > 0) {
-    l2_blur<T>(L, x, w0, w1, w2);             // w2 = k * x
-    l2_pad<T>(L, w2);
+    l2_blur<T, fe::kReplicate>(L, x, w0, w1, w2, l2_edge(L));   // w2 = k * x
     ub = w2;
   }
-  int rc = sweep_energy(L->ctx, L->ctx->stream, fe::kGrad, ub, w0, l2_vals(L) + kSlotE);   // w0 = g_ext
+  int rc = sweep_energy(L->ctx, L->ctx->stream, fe::kGrad, ub, w0, l2_vals(L) + kSlotE);
   if (rc) return rc;
   if (L->r > 0) {
-    l2_fold<T>(L, w0, w1);                    // w1 = gb
-    l2_blur<T>(L, w1, w0, w2, w1);           // w1 = k * gb (zero-extended)
-    l2_fold<T>(L, w1, g);
+    l2_blur<T, fe::kAdjoint>(L, w0, w1, w2, g, eo);
   } else {
-    l2_fold<T>(L, w0, g);
+    const fe::FieldDims d{L->box.nx, L->box.ny, L->box.nz, 1};
+    hipLaunchKernelGGL(fe::fold_shell<T>, dim3((unsigned)ceil_div(eo.nx * eo.ny, 256), (unsigned)eo.nz), dim3(256), 0,
+                       L->ctx->stream, (const T*)w0, g, d, eo);
   }
   FE_HIP(hipGetLastError());
   return FE_OK;
 }
 
-// As l2_eval_dev, with the loss copied to the host (syncs).
+// The same into the optimiser's gradient.
 template <typename T>
-int l2_eval(fe_l2* L, double& loss) {
-  int rc = l2_eval_dev<T>(L);
+int l2_eval_dev(fe_l2* L) {
+  return l2_eval_dev<T>(L, static_cast<T*>(L->g), l2_edge(L));
+}
+
+// As l2_eval_dev, the gradient into a dense box field (null: into the optimiser's),
+// with the loss copied to the host (syncs).
+template <typename T>
+int l2_eval(fe_l2* L, double& loss, T* g) {
+  int rc = g ? l2_eval_dev<T>(L, g, l2_dense(L)) : l2_eval_dev<T>(L);
   if (rc) return rc;
   rc = l2_read_slots(L, kSlotE, 1, &loss);
   if (rc) return rc;
@@ -476,15 +485,25 @@ int fe_l2_create(const fe_grid* grid, double eps, const double* p_coeffs, double
   if (!L) return set_error(FE_ENOMEM, "host allocation failed");
   L->sigma_k = sigma_k;
   L->r = sigma_k > 0.0 ? (int)std::ceil(4.0 * sigma_k) : 0;
-  const int W = std::max(1, L->r);
+  // the limits hold for a box with a margin as wide as the blur on every side
+  const int M = std::max(1, L->r);
+  fe_grid mg = *grid;
+  mg.nx += 2 * M;
+  mg.ny += 2 * M;
+  mg.nz += 2 * M;
+  if ((long)mg.nz > 65535 || (long)mg.ny > 65535 || !flow_dims_ok(mg)) {
+    l2_free(L);
+    return set_error(FE_EINVAL, "grid too large for the flow kernels");
+  }
+  if ((rc = check_grid(&mg))) {
+    l2_free(L);
+    return rc;
+  }
+  constexpr int W = 1;
   fe_grid pg = *grid;
   pg.nx += 2 * W;
   pg.ny += 2 * W;
   pg.nz += 2 * W;
-  if ((long)pg.nz > 65535 || (long)pg.ny > 65535 || !flow_dims_ok(pg)) {
-    l2_free(L);
-    return set_error(FE_EINVAL, "grid too large for the flow kernels");
-  }
   rc = fe_create(&pg, &eps, p_coeffs, stream, &L->ctx);
   if (rc) {
     l2_free(L);
@@ -582,16 +601,8 @@ int fe_l2_load(fe_l2* L, const void* u) {
   if (!L) return set_error(FE_EINVAL, "flow is NULL");
   if (!u) return set_error(FE_EINVAL, "u is NULL");
   DeviceGuard dg(L->ctx->device);
-  const size_t nbox = (size_t)(L->box.hi[0] - L->box.lo[0]) * (L->box.hi[1] - L->box.lo[1]) *
-                      (L->box.hi[2] - L->box.lo[2]);
-  const int nb = l2_launch_1d(nbox);
-  if (L->ctx->grid.dtype == FE_F32)
-    hipLaunchKernelGGL(fe::box_copy<float>, dim3(nb), dim3(256), 0, L->ctx->stream, static_cast<const float*>(u),
-                       static_cast<float*>(L->x), L->box, 1);
-  else
-    hipLaunchKernelGGL(fe::box_copy<double>, dim3(nb), dim3(256), 0, L->ctx->stream,
-                       static_cast<const double*>(u), static_cast<double*>(L->x), L->box, 1);
-  FE_HIP(hipGetLastError());
+  const int rc = l2_box_copy_any(L, u, L->x, 1);
+  if (rc) return rc;
   L->n_iter = 0;
   L->hist_len = 0;
   L->rho.clear();
@@ -605,17 +616,7 @@ int fe_l2_store(fe_l2* L, void* u) {
   if (!L) return set_error(FE_EINVAL, "flow is NULL");
   if (!u) return set_error(FE_EINVAL, "u is NULL");
   DeviceGuard dg(L->ctx->device);
-  const size_t nbox = (size_t)(L->box.hi[0] - L->box.lo[0]) * (L->box.hi[1] - L->box.lo[1]) *
-                      (L->box.hi[2] - L->box.lo[2]);
-  const int nb = l2_launch_1d(nbox);
-  if (L->ctx->grid.dtype == FE_F32)
-    hipLaunchKernelGGL(fe::box_copy<float>, dim3(nb), dim3(256), 0, L->ctx->stream,
-                       static_cast<const float*>(L->x), static_cast<float*>(u), L->box, 0);
-  else
-    hipLaunchKernelGGL(fe::box_copy<double>, dim3(nb), dim3(256), 0, L->ctx->stream,
-                       static_cast<const double*>(L->x), static_cast<double*>(u), L->box, 0);
-  FE_HIP(hipGetLastError());
-  return FE_OK;
+  return l2_box_copy_any(L, L->x, u, 0);
 }
 
 int fe_l2_energy_grad(fe_l2* L, const void* u, void* g, double* energy) {
@@ -623,21 +624,10 @@ int fe_l2_energy_grad(fe_l2* L, const void* u, void* g, double* energy) {
   if (rc) return rc;
   DeviceGuard dg(L->ctx->device);
   double E = 0.0;
-  rc = L->ctx->grid.dtype == FE_F32 ? l2_eval<float>(L, E) : l2_eval<double>(L, E);
+  rc = L->ctx->grid.dtype == FE_F32 ? l2_eval<float>(L, E, static_cast<float*>(g))
+                                    : l2_eval<double>(L, E, static_cast<double*>(g));
   if (rc) return rc;
   if (energy) *energy = E;
-  if (g) {
-    const size_t nbox = (size_t)(L->box.hi[0] - L->box.lo[0]) * (L->box.hi[1] - L->box.lo[1]) *
-                        (L->box.hi[2] - L->box.lo[2]);
-    const int nb = l2_launch_1d(nbox);
-    if (L->ctx->grid.dtype == FE_F32)
-      hipLaunchKernelGGL(fe::box_copy<float>, dim3(nb), dim3(256), 0, L->ctx->stream,
-                         static_cast<const float*>(L->g), static_cast<float*>(g), L->box, 0);
-    else
-      hipLaunchKernelGGL(fe::box_copy<double>, dim3(nb), dim3(256), 0, L->ctx->stream,
-                         static_cast<const double*>(L->g), static_cast<double*>(g), L->box, 0);
-    FE_HIP(hipGetLastError());
-  }
   return FE_OK;
 }
 
