@@ -80,46 +80,54 @@ __device__ __forceinline__ double bank_value(const double* __restrict__ bank) {
 
 // The block's combination of one value per thread into bank[blockIdx.x], in a
 // fixed order (each wave's butterfly, then the waves in order).
-template <int OP>
+template <int OP, int NT = kVecThreads>
 __device__ __forceinline__ void vec_block_partial(double acc, double* __restrict__ bank) {
-  __shared__ double s_w[kVecThreads / 64];
+  __shared__ double s_w[NT / 64];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc = vec_combine<OP>(acc, __shfl_xor(acc, off, 64));
   if (threadIdx.x % 64 == 0) s_w[threadIdx.x / 64] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
     double a = s_w[0];
-    for (int k = 1; k < kVecThreads / 64; ++k) a = vec_combine<OP>(a, s_w[k]);
+    for (int k = 1; k < NT / 64; ++k) a = vec_combine<OP>(a, s_w[k]);
     bank[blockIdx.x] = a;
   }
 }
 
-// Four consecutive vector elements, moved with 16-byte loads and stores (the
-// vectors are whole device allocations, so element 4k is 16-byte aligned).
+// Consecutive vector elements of 16 bytes, moved with one load or store (the vectors
+// are whole device allocations, so pack k is aligned). Two FP64 elements rather than
+// four: a wave's load then takes whole lines, and the threads' shares of a vector come
+// out more even (130^3: 2.1 rounds of 256 x 1024 threads with four, 4.2 with two). At
+// 130^3 and 20 history vectors vec_gram then runs 440 MB in 98 us with 1024 threads
+// per block; with four elements it took 124 us at its best, 256 threads.
 template <typename T>
-struct alignas(16) Pack4 {
-  T v[4];
+constexpr int kPack = 16 / (int)sizeof(T);
+
+template <typename T>
+struct alignas(16) Pack {
+  T v[kPack<T>];
 };
 
 // bank <- partials of sum a*b (OP 0), sum |a| (OP 1) or max |a| (OP 2),
 // accumulated in FP64 with one accumulator per element of a pack. Grid-stride
-// over packs of four, two packs of each vector in flight per thread; block 0
-// takes the n % 4 tail.
+// over packs, two packs of each vector in flight per thread; block 0
+// takes the tail.
 template <typename T, int OP>
 __global__ __launch_bounds__(kVecThreads) void vec_reduce(const T* __restrict__ a, const T* __restrict__ b, size_t n,
                                                           double* __restrict__ bank) {
-  const size_t n4 = n / 4, stride = (size_t)gridDim.x * blockDim.x;
-  const Pack4<T>* pa = reinterpret_cast<const Pack4<T>*>(a);
-  const Pack4<T>* pb = reinterpret_cast<const Pack4<T>*>(b);
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < n4; i0 += 2 * stride) {
-    Pack4<T> va[2], vb[2];
+  constexpr int P = kPack<T>;
+  const size_t np = n / P, stride = (size_t)gridDim.x * blockDim.x;
+  const Pack<T>* pa = reinterpret_cast<const Pack<T>*>(a);
+  const Pack<T>* pb = reinterpret_cast<const Pack<T>*>(b);
+  double acc[P] = {};
+  for (size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < np; i0 += 2 * stride) {
+    Pack<T> va[2], vb[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const size_t i = i0 + u * stride;
-      va[u] = Pack4<T>{};
-      vb[u] = Pack4<T>{};
-      if (i < n4) {
+      va[u] = Pack<T>{};
+      vb[u] = Pack<T>{};
+      if (i < np) {
         va[u] = pa[i];
         if (OP == 0) vb[u] = pb[i];
       }
@@ -127,14 +135,16 @@ __global__ __launch_bounds__(kVecThreads) void vec_reduce(const T* __restrict__ 
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
+      for (int k = 0; k < P; ++k)
         acc[k] = vec_combine<OP>(acc[k], OP == 0 ? double(va[u].v[k]) * double(vb[u].v[k]) : fabs(double(va[u].v[k])));
   }
-  if (blockIdx.x == 0 && threadIdx.x < n - 4 * n4) {
-    const size_t j = 4 * n4 + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < n - P * np) {
+    const size_t j = P * np + threadIdx.x;
     acc[0] = vec_combine<OP>(acc[0], OP == 0 ? double(a[j]) * double(b[j]) : fabs(double(a[j])));
   }
-  vec_block_partial<OP>(vec_combine<OP>(vec_combine<OP>(acc[0], acc[1]), vec_combine<OP>(acc[2], acc[3])), bank);
+  double v = vec_combine<OP>(acc[0], acc[1]);
+  if constexpr (P == 4) v = vec_combine<OP>(v, vec_combine<OP>(acc[2], acc[3]));
+  vec_block_partial<OP>(v, bank);
 }
 
 // ---- the L-BFGS direction through Gram matrices ----
@@ -146,10 +156,6 @@ __global__ __launch_bounds__(kVecThreads) void vec_reduce(const T* __restrict__ 
 // passes per iteration: vec_gram forms the new pair and every inner product
 // the recursion needs, vec_lincomb forms the direction from the coefficients.
 
-// Threads per vec_gram block: a full block for FP32; a quarter for FP64, whose
-// accumulators and packs need twice the registers.
-template <typename T>
-constexpr int gram_threads() { return sizeof(T) == 4 ? kVecThreads : kVecThreads / 4; }
 constexpr int kDotVecs = 24;    // history vectors per vec_gram pass (all of them up to history 12)
 constexpr int kCombVecs = 24;   // vectors per vec_lincomb pass (all 2m + 1 of them up to history 11)
 
@@ -188,19 +194,20 @@ __device__ __forceinline__ void vec_block_partials(double (&acc)[NV], int nv, do
 }
 
 // One pass of the Gram update. FORM: first y = g - prev_g and s = t d, stored,
-// and the banks 0..4 get y.y, y.s, y.g, g.g, g.s (NB = 5; otherwise NB = 0).
+// the banks 0..4 get y.y, y.s, y.g, g.g, g.s (NB = 5; otherwise NB = 0) and the
+// bank `gmax` max |g|.
 // The first NL list vectors V_k then give g.V_k in bank NB + k. The products
 // of y with the history need no pass of their own: y.V = g.V - prev_g.V, and
 // the host kept prev_g.V from the previous pass. All NL list entries are read
 // (the host points unused ones at g, and only the first `count` reach the
 // banks), so the loops have fixed trip counts and every value stays in
-// registers. FP64 accumulation, packs of four, block 0 takes the n % 4 tail.
-// Grid: kVecBlocks blocks of gram_threads<T>().
+// registers. FP64 accumulation, block 0 takes the tail.
+// Grid: kVecBlocks blocks of kVecThreads.
 template <typename T, bool FORM, int NL>
-__global__ __launch_bounds__(gram_threads<T>()) void vec_gram(const T* __restrict__ g, const T* __restrict__ prev_g,
+__global__ __launch_bounds__(kVecThreads) void vec_gram(const T* __restrict__ g, const T* __restrict__ prev_g,
                                                               const T* __restrict__ d, double t, T* __restrict__ y,
                                                               T* __restrict__ s, DotList<T> L, size_t n,
-                                                              double* __restrict__ banks) {
+                                                              double* __restrict__ banks, double* __restrict__ gmax) {
   static_assert(NL >= 0 && NL <= kDotVecs && (FORM || NL > 0), "vec_gram list width");
   constexpr int NB = FORM ? 5 : 0;
   constexpr int NV = NB + NL;
@@ -208,39 +215,42 @@ __global__ __launch_bounds__(gram_threads<T>()) void vec_gram(const T* __restric
   double acc[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = 0.0;
-  const size_t n4 = n / 4, stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-    const Pack4<T> pg = reinterpret_cast<const Pack4<T>*>(g)[i];
+  T mx = T(0);
+  constexpr int P = kPack<T>;
+  const size_t np = n / P, stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < np; i += stride) {
+    const Pack<T> pg = reinterpret_cast<const Pack<T>*>(g)[i];
     if constexpr (FORM) {
-      const Pack4<T> pp = reinterpret_cast<const Pack4<T>*>(prev_g)[i];
-      const Pack4<T> pd = reinterpret_cast<const Pack4<T>*>(d)[i];
-      Pack4<T> py, ps;
+      const Pack<T> pp = reinterpret_cast<const Pack<T>*>(prev_g)[i];
+      const Pack<T> pd = reinterpret_cast<const Pack<T>*>(d)[i];
+      Pack<T> py, ps;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < P; ++e) {
         py.v[e] = pg.v[e] - pp.v[e];
         ps.v[e] = tt * pd.v[e];
       }
-      reinterpret_cast<Pack4<T>*>(y)[i] = py;
-      reinterpret_cast<Pack4<T>*>(s)[i] = ps;
+      reinterpret_cast<Pack<T>*>(y)[i] = py;
+      reinterpret_cast<Pack<T>*>(s)[i] = ps;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < P; ++e) {
         const double ye = py.v[e], ge = pg.v[e], se = ps.v[e];
         acc[0] += ye * ye;
         acc[1] += ye * se;
         acc[2] += ye * ge;
         acc[3] += ge * ge;
         acc[4] += ge * se;
+        mx = fmax(mx, fabs(pg.v[e]));
       }
     }
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
-      const Pack4<T> pv = reinterpret_cast<const Pack4<T>*>(L.v[k])[i];
+      const Pack<T> pv = reinterpret_cast<const Pack<T>*>(L.v[k])[i];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[NB + k] += double(pg.v[e]) * double(pv.v[e]);
+      for (int e = 0; e < P; ++e) acc[NB + k] += double(pg.v[e]) * double(pv.v[e]);
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x < n - 4 * n4) {
-    const size_t j = 4 * n4 + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < n - P * np) {
+    const size_t j = P * np + threadIdx.x;
     const double ge = g[j];
     if constexpr (FORM) {
       const T yt = g[j] - prev_g[j], st = tt * d[j];
@@ -252,11 +262,13 @@ __global__ __launch_bounds__(gram_threads<T>()) void vec_gram(const T* __restric
       acc[2] += ye * ge;
       acc[3] += ge * ge;
       acc[4] += ge * se;
+      mx = fmax(mx, fabs(g[j]));
     }
 #pragma unroll
     for (int k = 0; k < NL; ++k) acc[NB + k] += ge * double(L.v[k][j]);
   }
-  vec_block_partials<NV, gram_threads<T>()>(acc, NB + L.count, banks);
+  vec_block_partials<NV, kVecThreads>(acc, NB + L.count, banks);
+  if constexpr (FORM) vec_block_partial<2, kVecThreads>(double(mx), gmax);
 }
 
 // out = sum_k c_k V_k (+ out when acc), accumulated in FP64 and rounded once;
@@ -265,42 +277,46 @@ __global__ __launch_bounds__(gram_threads<T>()) void vec_gram(const T* __restric
 // optimiser's step folded into the pass that forms its direction. All W list
 // entries are read (the host pads a short list with zero coefficients on a
 // listed vector), so the loop has a fixed trip count. Layout of the work as in
-// vec_reduce.
+// vec_reduce, but from the end: the last packs of the history are those that the
+// Gram pass before it read last, and part of them is still in the memory-side cache
+// (130^3 FP64, 21 vectors: 77 us; from the start 88).
 template <typename T, int W>
 __global__ __launch_bounds__(kVecThreads) void vec_lincomb(CombList<T> L, T* __restrict__ out, int acc, size_t n,
                                                            double* __restrict__ dmax, T* __restrict__ x, double t) {
   static_assert(W >= 1 && W <= kCombVecs, "vec_lincomb width");
-  const size_t n4 = n / 4, stride = (size_t)gridDim.x * blockDim.x;
+  constexpr int P = kPack<T>;
+  const size_t np = n / P, stride = (size_t)gridDim.x * blockDim.x;
   double mx = 0.0;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < np; q += stride) {
+    const size_t i = np - 1 - q;
+    double a[P] = {};
     if (acc) {
-      const Pack4<T> po = reinterpret_cast<const Pack4<T>*>(out)[i];
+      const Pack<T> po = reinterpret_cast<const Pack<T>*>(out)[i];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = double(po.v[e]);
+      for (int e = 0; e < P; ++e) a[e] = double(po.v[e]);
     }
 #pragma unroll
     for (int k = 0; k < W; ++k) {
-      const Pack4<T> pv = reinterpret_cast<const Pack4<T>*>(L.v[k])[i];
+      const Pack<T> pv = reinterpret_cast<const Pack<T>*>(L.v[k])[i];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] += L.c[k] * double(pv.v[e]);
+      for (int e = 0; e < P; ++e) a[e] += L.c[k] * double(pv.v[e]);
     }
-    Pack4<T> r;
+    Pack<T> r;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < P; ++e) {
       r.v[e] = T(a[e]);
       mx = fmax(mx, fabs(double(r.v[e])));
     }
-    reinterpret_cast<Pack4<T>*>(out)[i] = r;
+    reinterpret_cast<Pack<T>*>(out)[i] = r;
     if (x) {
-      Pack4<T> px = reinterpret_cast<const Pack4<T>*>(x)[i];
+      Pack<T> px = reinterpret_cast<const Pack<T>*>(x)[i];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) px.v[e] = T(double(px.v[e]) + t * double(r.v[e]));
-      reinterpret_cast<Pack4<T>*>(x)[i] = px;
+      for (int e = 0; e < P; ++e) px.v[e] = T(double(px.v[e]) + t * double(r.v[e]));
+      reinterpret_cast<Pack<T>*>(x)[i] = px;
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x < n - 4 * n4) {
-    const size_t j = 4 * n4 + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < n - P * np) {
+    const size_t j = P * np + threadIdx.x;
     double a = acc ? double(out[j]) : 0.0;
 #pragma unroll
     for (int k = 0; k < W; ++k) a += L.c[k] * double(L.v[k][j]);
@@ -312,26 +328,15 @@ __global__ __launch_bounds__(kVecThreads) void vec_lincomb(CombList<T> L, T* __r
   if (dmax) vec_block_partial<2>(mx, dmax);
 }
 
-// Values of `count` consecutive sum banks: out[k] = bank_value<0>(bank k).
-// Grid: count blocks of 64.
-__global__ __launch_bounds__(64) void vec_finish_sums(const double* __restrict__ banks, double* __restrict__ out) {
-  const double v = bank_value<0>(banks + (size_t)blockIdx.x * kVecBlocks);
-  if (threadIdx.x == 0) out[blockIdx.x] = v;
-}
-
-// Values of up to four banks for the host: out[k] = bank_value<op[k]>(bank[k]).
-struct BankList {
-  const double* bank[4];
-  double* out[4];
-  int op[4];
-  int count;
-};
-
-__global__ __launch_bounds__(64) void vec_finish(BankList l) {
-  for (int k = 0; k < l.count; ++k) {
-    const double v = l.op[k] == 2 ? bank_value<2>(l.bank[k]) : bank_value<0>(l.bank[k]);
-    if (threadIdx.x == 0) *l.out[k] = v;
-  }
+// Values of consecutive banks for the host: out[k] = bank_value(bank k), a maximum
+// for the banks whose bit is set in `maxima` (the first 32), else a sum. Grid: one
+// block of 64 per bank.
+__global__ __launch_bounds__(64) void vec_finish(const double* __restrict__ banks, double* __restrict__ out,
+                                                 unsigned maxima) {
+  const unsigned k = blockIdx.x;
+  const double* bank = banks + (size_t)k * kVecBlocks;
+  const double v = k < 32 && (maxima >> k & 1u) ? bank_value<2>(bank) : bank_value<0>(bank);
+  if (threadIdx.x == 0) out[k] = v;
 }
 
 // Copy between the box of a padded array and a dense box field [nz][ny][nx]: four

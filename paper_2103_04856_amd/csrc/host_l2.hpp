@@ -63,7 +63,6 @@ constexpr size_t kL2RedDoubles = (size_t)kL2Banks * fe::kVecBlocks + kL2Banks;
 
 double* l2_bank(fe_l2* L, int slot) { return L->d_red + (size_t)slot * fe::kVecBlocks; }
 double* l2_vals(fe_l2* L) { return L->d_red + (size_t)kL2Banks * fe::kVecBlocks; }
-int l2_slot_op(int slot) { return slot == kSlotGmax || slot == kSlotDmax ? 2 : slot == kSlotL1 ? 1 : 0; }
 
 const dim3 kVecGrid(fe::kVecBlocks), kVecBlock(fe::kVecThreads);
 
@@ -84,23 +83,16 @@ int l2_reduce_dev(fe_l2* L, int op, const void* a, const void* b, int slot) {
   return FE_OK;
 }
 
-// Host copies of the values of named slots [first, first + count) (one sync):
-// the banks among them are combined on the device first.
-int l2_read_slots(fe_l2* L, int first, int count, double* out) {
-  fe::BankList bl{};
-  for (int k = first; k < first + count; ++k) {
-    if (k == kSlotE) continue;
-    if (bl.count == 4) return set_error(FE_EINVAL, "internal: too many slots in one read");
-    bl.bank[bl.count] = l2_bank(L, k);
-    bl.out[bl.count] = l2_vals(L) + k;
-    bl.op[bl.count] = l2_slot_op(k);
-    ++bl.count;
-  }
-  if (bl.count) {
-    hipLaunchKernelGGL(fe::vec_finish, dim3(1), dim3(64), 0, L->ctx->stream, bl);
+// Host copies of the values of slots [0, count), the energy's among them (one sync);
+// the other slots' banks are combined on the device first.
+int l2_read_slots(fe_l2* L, int count, double* out) {
+  if (count > kSlotGmax) {
+    hipLaunchKernelGGL(fe::vec_finish, dim3(count - kSlotGmax), dim3(64), 0, L->ctx->stream,
+                       (const double*)l2_bank(L, kSlotGmax), l2_vals(L) + kSlotGmax,
+                       (1u << (kSlotGmax - kSlotGmax)) | (1u << (kSlotDmax - kSlotGmax)));
     FE_HIP(hipGetLastError());
   }
-  FE_HIP(hipMemcpyAsync(out, l2_vals(L) + first, sizeof(double) * count, hipMemcpyDeviceToHost, L->ctx->stream));
+  FE_HIP(hipMemcpyAsync(out, l2_vals(L), sizeof(double) * count, hipMemcpyDeviceToHost, L->ctx->stream));
   FE_HIP(hipStreamSynchronize(L->ctx->stream));
   return FE_OK;
 }
@@ -148,9 +140,10 @@ int l2_scale_add(fe_l2* L, double alpha, const void* x, bool acc, void* y) {
 }
 
 // The Gram pass: y = g - prev_g into L->q, s = t d into L->w0, and the inner
-// products y.y, y.s, y.g, g.g, g.s and, for every vector v of `hist`, g.v,
-// copied to `out` in that order (one sync). Up to kDotVecs history vectors go
-// through one pass; a list of 8, 16 or 24 entries, the unused ones pointing at g.
+// products y.y, y.s, y.g, g.g, g.s and g.v for every history vector v (S, then Y)
+// into the banks of kSlotGram on, and max |g| into kSlotGmax's; stream-ordered. Up to
+// kDotVecs history vectors go through one pass; a list of 8, 16 or 24 entries, the
+// unused ones pointing at g.
 template <typename T>
 void gram_launch(fe_l2* L, bool form, const fe::DotList<T>& dl, int bank) {
   hipStream_t s = L->ctx->stream;
@@ -160,54 +153,47 @@ void gram_launch(fe_l2* L, bool form, const fe::DotList<T>& dl, int bank) {
   T* y = static_cast<T*>(L->q);
   T* sv = static_cast<T*>(L->w0);
   double* bk = l2_bank(L, bank);
-  const dim3 grid = kVecGrid, blk(fe::gram_threads<T>());
+  double* gm = l2_bank(L, kSlotGmax);
+  const dim3 grid = kVecGrid, blk = kVecBlock;
   const int nl = dl.count == 0 ? 0 : dl.count <= 8 ? 8 : dl.count <= 16 ? 16 : fe::kDotVecs;
   if (form) {
     if (nl == 0)
-      hipLaunchKernelGGL((fe::vec_gram<T, true, 0>), grid, blk, 0, s, g, pg, d, L->t, y, sv, dl, L->n, bk);
+      hipLaunchKernelGGL((fe::vec_gram<T, true, 0>), grid, blk, 0, s, g, pg, d, L->t, y, sv, dl, L->n, bk, gm);
     else if (nl == 8)
-      hipLaunchKernelGGL((fe::vec_gram<T, true, 8>), grid, blk, 0, s, g, pg, d, L->t, y, sv, dl, L->n, bk);
+      hipLaunchKernelGGL((fe::vec_gram<T, true, 8>), grid, blk, 0, s, g, pg, d, L->t, y, sv, dl, L->n, bk, gm);
     else if (nl == 16)
-      hipLaunchKernelGGL((fe::vec_gram<T, true, 16>), grid, blk, 0, s, g, pg, d, L->t, y, sv, dl, L->n, bk);
+      hipLaunchKernelGGL((fe::vec_gram<T, true, 16>), grid, blk, 0, s, g, pg, d, L->t, y, sv, dl, L->n, bk, gm);
     else
       hipLaunchKernelGGL((fe::vec_gram<T, true, fe::kDotVecs>), grid, blk, 0, s, g, pg, d, L->t, y, sv, dl, L->n,
-                         bk);
+                         bk, gm);
   } else {
     if (nl == 8)
       hipLaunchKernelGGL((fe::vec_gram<T, false, 8>), grid, blk, 0, s, g, nullptr, nullptr, 0.0, nullptr, nullptr, dl,
-                         L->n, bk);
+                         L->n, bk, nullptr);
     else if (nl == 16)
       hipLaunchKernelGGL((fe::vec_gram<T, false, 16>), grid, blk, 0, s, g, nullptr, nullptr, 0.0, nullptr, nullptr,
-                         dl, L->n, bk);
+                         dl, L->n, bk, nullptr);
     else
       hipLaunchKernelGGL((fe::vec_gram<T, false, fe::kDotVecs>), grid, blk, 0, s, g, nullptr, nullptr, 0.0, nullptr,
-                         nullptr, dl, L->n, bk);
+                         nullptr, dl, L->n, bk, nullptr);
   }
 }
 
 template <typename T>
-int l2_gram(fe_l2* L, const std::vector<const void*>& hist, std::vector<double>& out) {
-  hipStream_t s = L->ctx->stream;
+int l2_gram_dev(fe_l2* L) {
   const T* g = static_cast<const T*>(L->g);
-  const size_t K = hist.size();
-  int bank = kSlotGram;
-  size_t k0 = 0;
+  const int m = L->hist_len, K = 2 * m;
+  int bank = kSlotGram, k0 = 0;
   do {
     fe::DotList<T> dl{};
-    dl.count = (int)std::min<size_t>(fe::kDotVecs, K - k0);
-    for (int k = 0; k < fe::kDotVecs; ++k) dl.v[k] = k < dl.count ? static_cast<const T*>(hist[k0 + k]) : g;
+    dl.count = std::min(fe::kDotVecs, K - k0);
+    for (int k = 0; k < fe::kDotVecs; ++k)
+      dl.v[k] = k >= dl.count ? g : static_cast<const T*>(k0 + k < m ? L->S[k0 + k] : L->Y[k0 + k - m]);
     gram_launch<T>(L, k0 == 0, dl, bank);
     FE_HIP(hipGetLastError());
     bank += (k0 == 0 ? 5 : 0) + dl.count;
     k0 += dl.count;
   } while (k0 < K);
-  const int nv = bank - kSlotGram;
-  hipLaunchKernelGGL(fe::vec_finish_sums, dim3(nv), dim3(64), 0, s, (const double*)l2_bank(L, kSlotGram),
-                     l2_vals(L) + kSlotGram);
-  FE_HIP(hipGetLastError());
-  out.resize(nv);
-  FE_HIP(hipMemcpyAsync(out.data(), l2_vals(L) + kSlotGram, sizeof(double) * nv, hipMemcpyDeviceToHost, s));
-  FE_HIP(hipStreamSynchronize(s));
   return FE_OK;
 }
 
@@ -286,9 +272,25 @@ template <typename T>
 int l2_eval(fe_l2* L, double& loss, T* g) {
   int rc = g ? l2_eval_dev<T>(L, g, l2_dense(L)) : l2_eval_dev<T>(L);
   if (rc) return rc;
-  rc = l2_read_slots(L, kSlotE, 1, &loss);
+  rc = l2_read_slots(L, 1, &loss);
   if (rc) return rc;
   if (!std::isfinite(loss)) return set_error(FE_ENONFINITE, "energy is not finite");
+  return FE_OK;
+}
+
+// The scalars of one evaluation: the energy, max|g|, max|d| of the last direction
+// and, unless the next iteration is the first ever, its Gram pass, which depends on
+// nothing that the host decides in between (its vectors are scratch if the step ends
+// here). One read for all of them: two reads per iteration left the device idle for
+// about 85 us, one for 45 (128^3 FP64, 20 iterations: 6.16 -> 5.50 ms).
+template <typename T>
+int l2_eval_scalars(fe_l2* L, bool gram, std::vector<double>& sc) {
+  int rc = l2_eval_dev<T>(L);
+  if (!rc) rc = gram ? l2_gram_dev<T>(L) : l2_reduce_dev<T>(L, 2, L->g, nullptr, kSlotGmax);
+  if (rc) return rc;
+  sc.resize(gram ? kSlotGram + 5 + 2 * L->hist_len : kSlotDmax + 1);
+  if ((rc = l2_read_slots(L, (int)sc.size(), sc.data()))) return rc;
+  if (!std::isfinite(sc[kSlotE])) return set_error(FE_ENONFINITE, "energy is not finite");
   return FE_OK;
 }
 
@@ -298,21 +300,17 @@ int l2_eval(fe_l2* L, double& loss, T* g) {
 // a pair (s, y) enters the history only if s'y > 1e-10. Stops early on
 // max|g| <= tol_grad, a non-descent direction (g'd > -tol_change), a step
 // max|t d| <= tol_change, or a loss change below tol_change. `loss0` receives
-// the loss at the start of the step. The recursion's dot products stay in
-// device scalar slots; the host reads scalars only where it branches on them
-// (about three syncs per iteration).
+// the loss at the start of the step. The host reads the scalars of an iteration
+// once, after its evaluation (l2_eval_scalars).
 template <typename T>
 int l2_step(fe_l2* L, double& loss0) {
-  int rc = l2_eval_dev<T>(L);
+  std::vector<double> sc;
+  int rc = l2_eval_scalars<T>(L, L->n_iter > 0, sc);
   if (rc) return rc;
-  if ((rc = l2_reduce_dev<T>(L, 2, L->g, nullptr, kSlotGmax))) return rc;
-  double sc[2];
-  if ((rc = l2_read_slots(L, kSlotE, 2, sc))) return rc;
-  double loss = sc[0], gmax = sc[1];
-  if (!std::isfinite(loss)) return set_error(FE_ENONFINITE, "energy is not finite");
+  double loss = sc[kSlotE];
   loss0 = loss;
   int evals = 1;
-  if (gmax <= L->tol_grad) return FE_OK;
+  if (sc[kSlotGmax] <= L->tol_grad) return FE_OK;
   bool opt_cond = false;
   for (int it = 1; it <= L->max_iter; ++it) {
     ++L->n_iter;
@@ -328,22 +326,18 @@ int l2_step(fe_l2* L, double& loss0) {
       L->H_diag = 1.0;
       if ((rc = l2_reduce_dev<T>(L, 0, L->g, L->d, kSlotGtd))) return rc;
       if ((rc = l2_reduce_dev<T>(L, 1, L->g, nullptr, kSlotL1))) return rc;
-      double gl[2];
-      if ((rc = l2_read_slots(L, kSlotGtd, 2, gl))) return rc;
-      gtd = gl[0];
-      gl1 = gl[1];
+      double gl[kSlotL1 + 1];
+      if ((rc = l2_read_slots(L, kSlotL1 + 1, gl))) return rc;
+      gtd = gl[kSlotGtd];
+      gl1 = gl[kSlotL1];
     } else {
-      // The Gram pass: y = g - prev_g (in q), s = t d (in w0), the inner
-      // products of y and g with each other and with s, and g with every
-      // history vector; y with a history vector is g.v - prev_g.v, the latter
+      // The Gram pass came with the evaluation: y = g - prev_g (in q), s = t d (in
+      // w0), the inner products of y and g with each other and with s, and g with
+      // every history vector; y with a history vector is g.v - prev_g.v, the latter
       // kept from the previous pass (prev_g was that pass's g).
       int m = L->hist_len;
       const int H = L->history;
-      std::vector<const void*> hist;
-      for (int i = 0; i < m; ++i) hist.push_back(L->S[i]);
-      for (int i = 0; i < m; ++i) hist.push_back(L->Y[i]);
-      std::vector<double> gv;
-      if ((rc = l2_gram<T>(L, hist, gv))) return rc;
+      const double* gv = sc.data() + kSlotGram;
       const double yy = gv[0], ys = gv[1], yg = gv[2], gg = gv[3], gs = gv[4];
       if ((int)L->pgS.size() != m || (int)L->pgY.size() != m)
         return set_error(FE_EINVAL, "L-BFGS state out of step with its history");
@@ -434,14 +428,10 @@ int l2_step(fe_l2* L, double& loss0) {
     if (!moved && (rc = l2_scale_add<T>(L, L->t, L->d, true, L->x))) return rc;   // max |d| is in its slot already
     double dmax = 0.0;
     if (it != L->max_iter) {
-      if ((rc = l2_eval_dev<T>(L))) return rc;
-      if ((rc = l2_reduce_dev<T>(L, 2, L->g, nullptr, kSlotGmax))) return rc;
-      double egd[3];
-      if ((rc = l2_read_slots(L, kSlotE, 3, egd))) return rc;
-      loss = egd[0];
-      if (!std::isfinite(loss)) return set_error(FE_ENONFINITE, "energy is not finite");
-      opt_cond = egd[1] <= L->tol_grad;
-      dmax = egd[2];
+      if ((rc = l2_eval_scalars<T>(L, true, sc))) return rc;
+      loss = sc[kSlotE];
+      opt_cond = sc[kSlotGmax] <= L->tol_grad;
+      dmax = sc[kSlotDmax];
       ls_evals = 1;
     }
     evals += ls_evals;
