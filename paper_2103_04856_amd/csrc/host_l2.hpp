@@ -24,7 +24,8 @@ struct fe_l2 {
   std::vector<double> SY, YY;    // [history][history]: s_a . y_b (a <= b) and y_a . y_b of the history
   std::vector<double> pgS, pgY;  // prev_g . s_a and prev_g . y_a for the current history
   int hist_len = 0;
-  double* d_red = nullptr;       // reduction banks, then their values (kL2Banks each)
+  double* d_red = nullptr;       // reduction banks
+  double* h_vals = nullptr;      // pinned: the values that the host reads, written by the device
   // settings
   double lr = 1.0, tol_grad = 1e-7, tol_change = 1e-9;
   int history = 10, max_iter = 20, max_eval = 25;
@@ -54,15 +55,14 @@ int l2_box_copy_any(fe_l2* L, const void* src, void* dst, int to_padded) {
 // Scalars of the optimiser. Named slots: 0 energy, 1 max|g|, 2 max|d|, 3 g'd
 // and 4 |g|_1 (first iteration); then the inner products of the Gram pass
 // (y.y, y.s, y.g, g.g, g.s, then g.V_k for each history vector). d_red
-// holds one bank of kVecBlocks partials per slot, then one value per slot for
-// the host (the energy is written there directly).
+// holds one bank of kVecBlocks partials per slot; the values go to pinned host
+// memory, one per slot (the sweep's finish writes the energy there directly).
 constexpr int kSlotE = 0, kSlotGmax = 1, kSlotDmax = 2, kSlotGtd = 3, kSlotL1 = 4, kSlotGram = 5;
 constexpr int kL2MaxHistory = 64;
 constexpr int kL2Banks = kSlotGram + 5 + 2 * kL2MaxHistory;
-constexpr size_t kL2RedDoubles = (size_t)kL2Banks * fe::kVecBlocks + kL2Banks;
+constexpr size_t kL2RedDoubles = (size_t)kL2Banks * fe::kVecBlocks;
 
 double* l2_bank(fe_l2* L, int slot) { return L->d_red + (size_t)slot * fe::kVecBlocks; }
-double* l2_vals(fe_l2* L) { return L->d_red + (size_t)kL2Banks * fe::kVecBlocks; }
 
 const dim3 kVecGrid(fe::kVecBlocks), kVecBlock(fe::kVecThreads);
 
@@ -84,16 +84,17 @@ int l2_reduce_dev(fe_l2* L, int op, const void* a, const void* b, int slot) {
 }
 
 // Host copies of the values of slots [0, count), the energy's among them (one sync);
-// the other slots' banks are combined on the device first.
+// the other slots' banks are combined on the device first, which writes them to the
+// host itself.
 int l2_read_slots(fe_l2* L, int count, double* out) {
   if (count > kSlotGmax) {
     hipLaunchKernelGGL(fe::vec_finish, dim3(count - kSlotGmax), dim3(64), 0, L->ctx->stream,
-                       (const double*)l2_bank(L, kSlotGmax), l2_vals(L) + kSlotGmax,
+                       (const double*)l2_bank(L, kSlotGmax), L->h_vals + kSlotGmax,
                        (1u << (kSlotGmax - kSlotGmax)) | (1u << (kSlotDmax - kSlotGmax)));
     FE_HIP(hipGetLastError());
   }
-  FE_HIP(hipMemcpyAsync(out, l2_vals(L), sizeof(double) * count, hipMemcpyDeviceToHost, L->ctx->stream));
   FE_HIP(hipStreamSynchronize(L->ctx->stream));
+  std::copy_n(L->h_vals, count, out);
   return FE_OK;
 }
 
@@ -247,7 +248,7 @@ int l2_eval_dev(fe_l2* L, T* g, const fe::EdgeBox& eo) {
     l2_blur<T, fe::kReplicate>(L, x, w0, w1, w2, l2_edge(L));   // w2 = k * x
     ub = w2;
   }
-  int rc = sweep_energy(L->ctx, L->ctx->stream, fe::kGrad, ub, w0, l2_vals(L) + kSlotE);
+  int rc = sweep_energy(L->ctx, L->ctx->stream, fe::kGrad, ub, w0, L->h_vals + kSlotE);
   if (rc) return rc;
   if (L->r > 0) {
     l2_blur<T, fe::kAdjoint>(L, w0, w1, w2, g, eo);
@@ -448,6 +449,7 @@ int l2_free(fe_l2* L) {
   if (!L) return FE_OK;
   for (void* p : {L->x, L->g, L->w0, L->w1, L->w2, L->d, L->prev_g, L->q, (void*)L->d_red})
     if (p) (void)hipFree(p);
+  pinned_give(L->h_vals, kL2Banks);
   for (void* p : L->S)
     if (p) (void)hipFree(p);
   for (void* p : L->Y)
@@ -526,6 +528,10 @@ int fe_l2_create(const fe_grid* grid, double eps, const double* p_coeffs, double
     L->d_red = nullptr;
     l2_free(L);
     return set_error(FE_ENOMEM, "L2 flow reduction buffer allocation failed");
+  }
+  if (!(L->h_vals = pinned_take(kL2Banks))) {
+    l2_free(L);
+    return set_error(FE_ENOMEM, "L2 flow result buffer allocation failed");
   }
   if (hipMemsetAsync(L->d_red, 0, sizeof(double) * kL2RedDoubles, c->stream) != hipSuccess) {
     l2_free(L);
