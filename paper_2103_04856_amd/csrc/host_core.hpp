@@ -453,13 +453,24 @@ struct Geometry {
 // r < slots blocks (r / slots)^0.6 per plane (0.66 for one of two: alone it
 // hides less latency, yet finishes sooner). Fitted to the step sweep on 100^3
 // to 256^3 grids, one and 16 instances, two blocks per CU.
-double sweep_cost(long blocks, int num_cu, int slots, int L) {
+double sweep_cost(long blocks, int num_cu, int slots, int L, double share = 0.6) {
   const long k = (blocks + num_cu - 1) / num_cu;
   const long rest = k % slots;
   double t = (double)(k / slots) * L;
-  if (rest) t += L * std::pow((double)rest / slots, 0.6);
+  if (rest) t += L * std::pow((double)rest / slots, share);
   return t;
 }
+
+// The same model for the gradient sweeps: the planes that a chunk of l costs beyond
+// its own, the share's exponent and the most slots counted (the trace body fits four
+// blocks, but is near its memory rate with three). Fitted to 72 gradient sweeps, three
+// bodies, both precisions, 64^3 to 600 x 100 x 100 and 1 to 16 instances, over all
+// chunk lengths: the chosen one costs 0.25 % (trace body 1.1 %) more than the best one
+// on average; 2 planes, 0.6 and every slot cost 0.4 % (2.2 %). 16 x 100^3 FP32 without
+// S terms: 25 planes, 85.8 us, against 13 and 94.0; 160 x 224 x 160, trace body: 12
+// and 25.1 against 6 and 27.3. The steps keep their chunks: their mass sums follow them.
+constexpr int kGradExtra = 3, kGradSlots = 3;
+constexpr double kGradShare = 0.5;
 
 // The z chunk length of a halo-1 sweep (the energy-only and diagnostics sweeps)
 // over `cols` tile columns that sweep_cost finishes first, a chunk of l planes
@@ -481,7 +492,7 @@ int halo1_chunk(long cols, int nz, int num_cu, int slots) {
 
 // `slots`: blocks of the launched kernel that one compute unit holds at once
 // (used when lz_req is 0, automatic).
-Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, int slots) {
+Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, int slots, int kind) {
   const Variant& v = variants()[variant];
   Geometry g;
   g.ntx = ceil_div(grid.nx, v.tx);
@@ -499,7 +510,10 @@ Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, i
     for (int nzc = 1; nzc <= nz; ++nzc) {
       const int l = ceil_div(nz, nzc);
       if (nzc > 1 && l == ceil_div(nz, nzc - 1)) continue;   // the same chunks as nzc - 1
-      const double t = sweep_cost(cols * ceil_div(nz, l), num_cu, slots, l + 2);
+      const long blocks = cols * ceil_div(nz, l);
+      const double t = kind == fe::kGrad
+                           ? sweep_cost(blocks, num_cu, std::min(slots, kGradSlots), l + kGradExtra, kGradShare)
+                           : sweep_cost(blocks, num_cu, slots, l + 2);
       if (lz <= 0 || t < best) {
         best = t;
         lz = l;
@@ -538,7 +552,7 @@ int launch_slots(const fe_ctx* c, int variant, int kind) {
 
 // Launch geometry of a sweep of `kind` with `variant` on this context.
 Geometry geometry(const fe_ctx* c, int variant, int lz_req, int kind) {
-  return geometry_of(c->grid, c->num_cu, variant, lz_req, lz_req > 0 ? 1 : launch_slots(c, variant, kind));
+  return geometry_of(c->grid, c->num_cu, variant, lz_req, lz_req > 0 ? 1 : launch_slots(c, variant, kind), kind);
 }
 
 bool has_sp(int v, int dtype) {

@@ -77,7 +77,8 @@ int noalloc_sweep(const fe_grid& grid, const double* eps, const double* a, const
   int slots = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&slots, (const void*)fn, v.nt, 0) != hipSuccess || slots < 1)
     slots = 1;
-  const Geometry geo = g ? geometry_of(grid, slot.num_cu, vi, 0, slots) : energy_geometry(grid, slot.num_cu);
+  const Geometry geo =
+      g ? geometry_of(grid, slot.num_cu, vi, 0, slots, fe::kGrad) : energy_geometry(grid, slot.num_cu);
   const size_t nblocks = (size_t)geo.per_inst * grid.batch;
   if (nblocks > kScratchPartials)
     return set_error(FE_EINVAL, "grid needs %zu block partials; the static scratch holds %zu", nblocks,
