@@ -564,6 +564,16 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad
     slo[j] = COLS && j == 1 ? slo[0] + UX * (unsigned)sizeof(T)
                             : stencil_base<T, UX>((v / RX + 1) * UX + v % RX + 1);
   }
+  // BOX: whether a ring voxel's column lies in the box, formed once per block
+  bool in_column[BOX ? NS : 1];
+  if (BOX) {
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      const int v = ring_pos(j);
+      const int gx = wrap_index(x0 - 1 + v % RX, a.nx), gy = wrap_index(y0 - 1 + v / RX, a.ny);
+      in_column[j] = gx >= a.box_lo[0] && gx < a.box_hi[0] && gy >= a.box_lo[1] && gy < a.box_hi[1];
+    }
+  }
   // SP: in-plane offsets of this thread's ring voxels and their coefficients
   const size_t vol = plane * a.nz;
   const VoxelCoeffs<T>* cfb = SP ? coeff_records(a.cfield) + (size_t)bt.inst * vol : nullptr;
@@ -698,9 +708,7 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad
     // the density of ring item j and its adjoint from the stencil st
     auto adjoint = [&](int j, const Stencil19<T>& st, VoxelAdjoint<T>& ad) -> T {
       if (BOX) {
-        const int v = ring_pos(j);
-        const int gx = wrap_index(x0 - 1 + v % RX, a.nx), gy = wrap_index(y0 - 1 + v / RX, a.ny);
-        if (!zin || gx < a.box_lo[0] || gx >= a.box_hi[0] || gy < a.box_lo[1] || gy >= a.box_hi[1]) {
+        if (!zin || !in_column[BOX ? j : 0]) {
           ad = VoxelAdjoint<T>{};
           return T(0);
         }
