@@ -29,7 +29,9 @@ struct FlowRule {
 
 // Launch shapes of the flow kernels; the blur passes over n = (nx, ny, nz) voxels,
 // the field's or a box's.
-dim3 x_grid(const fe::FieldDims& n) { return dim3(ceil_div(n.nx, 64), ceil_div(n.ny, fe::kBlurRows), n.nz * n.batch); }
+dim3 x_grid(const fe::FieldDims& n, bool rows) {
+  return dim3((rows ? 1 : ceil_div(n.nx, 64)) * ceil_div(n.ny, fe::kBlurRows), 1, n.nz * n.batch);
+}
 dim3 axis_grid(const fe::FieldDims& n, int axis) {
   return axis == 1 ? dim3(ceil_div(n.nz * n.nx, 256), ceil_div(n.ny, fe::kAxisChunk), n.batch)
                    : dim3(ceil_div(n.nx * n.ny, 256), ceil_div(n.nz, fe::kAxisChunk), n.batch);
@@ -60,8 +62,7 @@ void blur_x_pass(hipStream_t s, const fe::FieldDims& d, const fe::BlurTaps<T>& k
                  const double* m0, const T* mfield, T inv2h, fe::FlowClock* clk, double beta1, double beta2,
                  const fe::EdgeBox& e = {}) {
   const fe::FieldDims n = pass_dims<EDGE>(d, e);
-  const dim3 g = x_grid(n), b(64, 4);
-  const dim3 gr(1, g.y, g.z);
+  const dim3 g = x_grid(n, false), gr = x_grid(n, true), b(64, 4);
   if constexpr (EDGE == fe::kPeriodic) {
     if (k.r == 4 && rows_fit(n, 4))
       hipLaunchKernelGGL((fe::blur_x<T, DIV, 4, true>), gr, b, 0, s, in, out, m0, mfield, d, inv2h, k, clk, beta1,
