@@ -273,11 +273,10 @@ int fe_diagnostics(fe_ctx* ctx, const void* u, void* curv, double* hist, int nbi
 /*
  * Algorithm 2 (Sec. 4.2): the L2 flow of F_h(k * u) with replicate boundary
  * conditions, driven by L-BFGS, on one field (the validation flow of the
- * paper's Willmore experiments). The box field [nz][ny][nx] is held inside a
- * padded copy whose padding repeats the nearest box voxel wherever a stencil
- * or the blur reads outside the box; F_h sums the density over the box only,
- * and derivatives that land on padding are added back onto the voxels it
- * copies, so the gradient is exact for that finite sum.
+ * paper's Willmore experiments). Wherever a stencil or the blur reads outside
+ * the box field [nz][ny][nx] it takes the nearest box voxel; F_h sums the
+ * density over the box only, and derivatives that land outside are added back
+ * onto the voxels read there, so the gradient is exact for that finite sum.
  *
  * L-BFGS (Nocedal and Wright's two-loop recursion, H0 = s'y / y'y, no line
  * search): each step runs up to max_iter inner iterations of fixed length lr
@@ -292,7 +291,7 @@ typedef struct fe_l2 fe_l2;
 /* grid: the box (batch must be 1); eps, p_coeffs[6] as in fe_create; blur
  * 0 <= sigma_k <= 4 voxels (0: none). The box padded by max(1, ceil(4 sigma_k))
  * on every side must have ny, nz <= 65535, planes under 4 GiB and
- * nz * nx < 2^31 (FE_EINVAL otherwise). Allocates the padded fields and the
+ * nz * nx < 2^31 (FE_EINVAL otherwise). Allocates the work fields and the
  * optimiser's history on the device. */
 int fe_l2_create(const fe_grid* grid, double eps, const double* p_coeffs, double sigma_k, void* stream,
                  fe_l2** out);

@@ -176,7 +176,7 @@ struct SweepArgs {
   const T* cfield;              // space-dependent coefficients: [batch][nz][ny][nx] records of the six
                                 // scaled C1..C6 (VoxelCoeffs), read by the SP instantiations only
   int box_lo[3], box_hi[3];     // BOX instantiations: the voxels (x, y, z) whose density is summed;
-                                // the others only supply samples (a padded field)
+                                // the others lie outside it
   GridConsts<T> k;
   T tau;                        // GD step size, or Adam learning rate
   T beta1, beta2, adam_eps;     // Adam
@@ -365,8 +365,8 @@ __device__ __forceinline__ BlockTile block_tile(const SweepArgs<T>& a) {
 // (a batch that mixes p symmetric in k1, k2 with others); kBodyNoS, kBodyFull and
 // kBodyTrace hold one body only, for batches whose instances all take it: a
 // single body needs fewer registers (FP32 32 x 32 tiles: step without S~ terms
-// 81 VGPRs against 116 with both bodies; Adam 96 and 123 against 130, where
-// both bodies leave one block per CU).
+// 75 VGPRs against 108 with both bodies, so three blocks per CU instead of two;
+// Adam 92 against 119).
 // SP: the coefficients C1..C6 come per voxel from a.cfield (loaded for every
 // ring voxel of a plane right after the plane is staged, so their latency
 // overlaps the barrier) instead of from the instance's parameters.

@@ -53,7 +53,7 @@ struct Variant {
   Kernels<double> k64;
   Kernels<float> k32sp;    // with a coefficient field (only some variants have them)
   Kernels<double> k64sp;
-  std::array<SweepFn<float>, kBodies> k32box{};   // gradient with a box mask (padded, non-periodic fields)
+  std::array<SweepFn<float>, kBodies> k32box{};   // gradient with a box mask (non-periodic fields)
   std::array<SweepFn<double>, kBodies> k64box{};
   bool lead = false;   // a default candidate: chosen by the ring work its tiles cover a grid with
 };
@@ -84,7 +84,7 @@ Kernels<T> make_kernels() {
   return k;
 }
 
-// The gradient kernels of a box mask (padded, non-periodic fields) for a launch
+// The gradient kernels of a box mask (non-periodic fields) for a launch
 // shape, by body like Kernels.
 template <typename T, int TX, int TY, int NT, bool BODIES = false>
 std::array<SweepFn<T>, kBodies> make_box_kernels() {
@@ -133,11 +133,10 @@ const std::vector<Variant>& variants() {
     // small and the smallest tile of each precision (not for 50 x 20 with a
     // coefficient field: 134 VGPRs, one block per CU). 32 x 32 and 50 x 20 lead
     // the FP32 list: the same block (512 threads, three u loads and three ring
-    // voxels per thread, 48 KiB of LDS, two blocks per CU) over a tile whose
+    // voxels per thread, 47 KiB of LDS, two or three blocks per CU) over a tile whose
     // ring is 1.13 or 1.14 of it. 32 x 32 covers power-of-two planes exactly,
     // 50 x 20 planes of 100, 200 or 600 (where 32 x 32 computes 1.85x the
-    // plane at 100^2). 256^3 step, symmetric p: 94 us against 95 (64 x 16)
-    // and 97 (64 x 32 / 1024).
+    // plane at 100^2).
     add32(32, 32, 512, make_kernels<float, 32, 32, 512, false, true>());
     r.back().lead = true;
     add32(50, 20, 512, make_kernels<float, 50, 20, 512, false, true>(), {},
@@ -253,7 +252,7 @@ struct fe_ctx {
   bool use_cfield = false;
   void* d_mfield = nullptr;           // mass field m(x) [batch][nz][ny][nx] of the flow (Sec. 5.2)
   bool use_mfield = false;
-  bool use_box = false;               // padded non-periodic field: density only inside the box
+  bool use_box = false;               // non-periodic field: density only inside the box
   int box_lo[3] = {0, 0, 0}, box_hi[3] = {0, 0, 0};
   size_t max_blocks = 0;              // per instance, over all variants and z chunks
   int variant = -1;
@@ -692,7 +691,8 @@ int finish_sums(fe_ctx* c, hipStream_t s, const double* partials, double* energy
 // FP64 (64 x 8, 119 VGPRs): two blocks per CU. 256^3 FP32, measured against 3
 // and 4 rows per thread, 4 and 16 waves per block and chunks of 8 to 64
 // planes: 31.5 us (symmetric p) and 47 us (full body) at 32-plane chunks, the
-// makespan model's choice, within 2% of the fastest of those shapes.
+// makespan model's choice, within 2% of the fastest of those shapes (a p of
+// k1 + k2 alone: 23.4 us).
 constexpr int kEnergyWaves = 8;
 int energy_rows(int dtype) { return dtype == FE_F32 ? 2 : 1; }
 

@@ -2,17 +2,17 @@
 // L-BFGS) and its entry points. Included once by fe_api.hip.
 #pragma once
 
-// The optimiser state lives in device vectors of the padded layout (zero
-// padding); its scalars are FP64 on the host.
+// The optimiser state lives in device vectors of the box with a margin of one voxel
+// (zeros); its scalars are FP64 on the host.
 struct fe_l2 {
-  fe_ctx* ctx = nullptr;         // the padded grid, box mode
+  fe_ctx* ctx = nullptr;         // the grid with the margin, box mode
   fe::PadBox box{};
   double sigma_k = 0.0;
   int r = 0;                     // blur radius
-  size_t n = 0;                  // padded elements
+  size_t n = 0;                  // elements with the margin
   size_t esz = 0;
-  void* x = nullptr;             // the variable u (box plus replicated padding)
-  void* g = nullptr;             // dF/du (zero padding)
+  void* x = nullptr;             // the variable u (its margin is never read)
+  void* g = nullptr;             // dF/du (zero margin)
   void* w0 = nullptr;            // work fields
   void* w1 = nullptr;
   void* w2 = nullptr;
