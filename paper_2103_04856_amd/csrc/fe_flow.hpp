@@ -173,22 +173,25 @@ __device__ __forceinline__ T taps_dot(const BlurTaps<T>& k, const T* v, int step
   return acc;
 }
 
-// Blur along x of row segments: a block is kBlurRows rows x 64 x-values
+// Blur along x of row segments: a block is kBlurRows<ROWS> rows x 64 x-values
 // (block (64, 4), each thread on kBlurRows / 4 rows; grid (ceil(nx/64)
 // ceil(ny/kBlurRows), 1, nz * batch), x tiles fastest: the second grid axis would
-// limit ny); each row's segment and its periodic halo of r go through LDS. With DIV the loaded value is div A + m0 (the field of
-// Algorithm 1; m(x) from mfield instead of the instance's m0 when given, the
-// space-dependent mass of Sec. 5.2) and block (0,0,0) advances the clock (when
-// given); without, it is in[]. r = 0 is a plain copy (or div). All loads of a thread are issued
-// before the first LDS write, so a block keeps many in flight.
+// limit ny); each row's segment and its periodic halo of r go through LDS. With DIV
+// the loaded value is div A + m0 (the field of Algorithm 1; m(x) from mfield instead
+// of the instance's m0 when given, the space-dependent mass of Sec. 5.2) and block
+// (0,0,0) advances the clock (when given); without, it is in[]. r = 0 is a plain copy
+// (or div). All loads of a thread are issued before the first LDS write, so a block
+// keeps many in flight.
 // ROWS: rows with nx + 2r <= 128 are staged whole (x0 = 0, one x tile, grid
 // (ceil(ny/kBlurRows), 1, nz * batch)): a row of 100 then stages 116 samples
 // instead of two 64-wide tiles' 2 x (64 + 2r), and 100 of 128 lanes form outputs.
-// Rows per block, with the divergence and r = 8: the pass waits for its six loads per
-// sample, so more blocks with fewer rows each hide more of them, until a block is too
-// short (16 x 100^3 FP32, 256 MB to move: 4 rows 88 us, 8 rows 66, 12 rows 71,
-// 16 rows 74, 20 rows 74; 100^3: 7.5, 6.6, 6.7, 7.5, 7.4).
-constexpr int kBlurRows = 8;
+// Rows per block, with the divergence and r = 8. The pass waits for its six loads per
+// sample: with whole rows, more blocks with fewer rows each hide more of them, until
+// a block is too short (16 x 100^3 FP32, 256 MB to move: 4 rows 88 us, 8 rows 66, 12
+// rows 71, 16 rows 74, 20 rows 74; 100^3: 7.5, 6.6, 6.7, 7.5, 7.4). Rows in tiles of 64
+// have the blocks already (600 x 100 x 100: 8 rows 36.0 us, 16 rows 34.0).
+template <bool ROWS>
+constexpr int kBlurRows = ROWS ? 8 : 16;
 constexpr int kRowsMax = 128;   // ROWS: the longest staged row, nx + 2r
 
 template <typename T, bool DIV, int R = -1, bool ROWS = false, int EDGE = kPeriodic>
@@ -199,8 +202,8 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
   static_assert(!DIV || EDGE == kPeriodic, "the divergence is periodic");
   constexpr int kW = ROWS ? kRowsMax : 64 + 2 * kBlurMaxR;
   constexpr int kPer = (kW + 63) / 64;          // segment elements per thread and row
-  constexpr int kR = kBlurRows / 4;             // rows per thread
-  __shared__ T s[kBlurRows][kW];
+  constexpr int kR = kBlurRows<ROWS> / 4;             // rows per thread
+  __shared__ T s[kBlurRows<ROWS>][kW];
   if (DIV && clk && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0 &&
       threadIdx.y == 0) {
     const int t = clk->t + 1;
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
   T v[kR][kPer][7];          // the non-DIV form uses [0] only; [6] holds m(x)
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
-    const int y = ty * kBlurRows + wy + 4 * i;
+    const int y = ty * kBlurRows<ROWS> + wy + 4 * i;
     if (y >= ny) continue;
     const T* row = EDGE == kPeriodic ? base + (size_t)z * plane + (size_t)y * d.nx
                                      : base + (size_t)z * plane + (size_t)(e.lo + y) * d.nx + e.lo;
@@ -265,7 +268,7 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
   const T mass = (DIV && !mfield) ? T(m0[b]) : T(0);
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
-    const int y = ty * kBlurRows + wy + 4 * i;
+    const int y = ty * kBlurRows<ROWS> + wy + 4 * i;
     if (y >= ny) continue;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(256) void blur_x(const T* __restrict__ in, T* __res
     if (x >= nx) break;
 #pragma unroll
     for (int i = 0; i < kR; ++i) {
-      const int y = ty * kBlurRows + wy + 4 * i;
+      const int y = ty * kBlurRows<ROWS> + wy + 4 * i;
       if (y >= ny) continue;
       T* orow = EDGE == kPeriodic ? out + (size_t)b * vol + (size_t)z * plane + (size_t)y * d.nx
                                   : out + e.ooff + (size_t)t.z * e.oplane + (size_t)y * e.orow;

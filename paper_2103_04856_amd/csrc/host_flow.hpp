@@ -30,7 +30,8 @@ struct FlowRule {
 // Launch shapes of the flow kernels; the blur passes over n = (nx, ny, nz) voxels,
 // the field's or a box's.
 dim3 x_grid(const fe::FieldDims& n, bool rows) {
-  return dim3((rows ? 1 : ceil_div(n.nx, 64)) * ceil_div(n.ny, fe::kBlurRows), 1, n.nz * n.batch);
+  return rows ? dim3(ceil_div(n.ny, fe::kBlurRows<true>), 1, n.nz * n.batch)
+              : dim3(ceil_div(n.nx, 64) * ceil_div(n.ny, fe::kBlurRows<false>), 1, n.nz * n.batch);
 }
 dim3 axis_grid(const fe::FieldDims& n, int axis) {
   return axis == 1 ? dim3(ceil_div(n.nz * n.nx, 256), ceil_div(n.ny, fe::kAxisChunk), n.batch)
