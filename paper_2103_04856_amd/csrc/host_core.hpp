@@ -278,8 +278,12 @@ struct PinnedSlab {
 PinnedSlab g_pinned;
 constexpr int kPinnedUnit = 64, kPinnedUnits = 64;
 
+int pinned_units(size_t doubles) {
+  return (int)std::min<size_t>((doubles + kPinnedUnit - 1) / kPinnedUnit, kPinnedUnits);
+}
+
 unsigned long long pinned_mask(size_t doubles) {
-  const size_t units = (doubles + kPinnedUnit - 1) / kPinnedUnit;
+  const int units = pinned_units(doubles);
   return units < kPinnedUnits ? (1ull << units) - 1 : 0;   // 0: not from the slab
 }
 
@@ -294,7 +298,7 @@ double* pinned_take(size_t doubles) {
   if (const unsigned long long m = pinned_mask(doubles)) {
     std::lock_guard<std::mutex> lock(g_pinned.mu);
     if (!g_pinned.base) g_pinned.base = pinned_alloc((size_t)kPinnedUnit * kPinnedUnits);
-    for (int k = 0; g_pinned.base && (m << k >> k) == m; ++k)
+    for (int k = 0; g_pinned.base && k + pinned_units(doubles) <= kPinnedUnits; ++k)
       if (!(g_pinned.used & m << k)) {
         g_pinned.used |= m << k;
         return g_pinned.base + (size_t)k * kPinnedUnit;
