@@ -844,6 +844,14 @@ int adam_reset_launch(fe_ctx* c) {
   return FE_OK;
 }
 
+// The key of a captured loop: the caller's field, rule and loop length, and all that
+// the context's launches depend on beyond the device tables they read (its launch
+// shape, its fields and the sweeps' body, which fe_set_params can change).
+GraphKey graph_key(const fe_ctx* c, void* u, const StepRule& rule, double sigma, int pairs) {
+  return GraphKey{u,     rule.mode, rule.tau,         rule.beta1, rule.beta2,       rule.adam_eps,
+                  sigma, pairs,     sweep_variant(c), c->lz,      fields_in_use(c), c->body};
+}
+
 int run_steps(fe_ctx* c, void* u, const double* mass, const StepRule& rule, int nsteps, double* energy) {
   if (!u) return set_error(FE_EINVAL, "u is NULL");
   if (!mass) return set_error(FE_EINVAL, "mass is NULL");
@@ -893,8 +901,7 @@ int run_steps(fe_ctx* c, void* u, const double* mass, const StepRule& rule, int 
   if (gpairs > 0) {
     if ((rc = tick(c->stream, pending))) return rc;
     pending = 0;
-    GraphKey key{u,      rule.mode,           rule.tau, rule.beta1,       rule.beta2, rule.adam_eps, 0.0,
-                 gpairs, sweep_variant(c), c->lz,    fields_in_use(c), c->body};
+    const GraphKey key = graph_key(c, u, rule, 0.0, gpairs);
     auto it = c->graphs.find(key);
     hipGraphExec_t exec = nullptr;
     if (it == c->graphs.end()) {

@@ -248,7 +248,7 @@ int fe_hminus_step(fe_ctx* c, void* A, const double* m0, double sigma_k, double 
     if (rc) return rc;
   }
   if (gi > 0) {
-    GraphKey key{A, kFlowMode, lr, beta1, beta2, adam_eps, sigma_k, gi, sweep_variant(c), c->lz, fields_in_use(c)};
+    const GraphKey key = graph_key(c, A, StepRule{kFlowMode, lr, beta1, beta2, adam_eps}, sigma_k, gi);
     auto it = c->graphs.find(key);
     hipGraphExec_t exec = nullptr;
     if (it == c->graphs.end()) {
