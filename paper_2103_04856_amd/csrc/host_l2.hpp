@@ -24,8 +24,8 @@ struct fe_l2 {
   std::vector<double> SY, YY;    // [history][history]: s_a . y_b (a <= b) and y_a . y_b of the history
   std::vector<double> pgS, pgY;  // prev_g . s_a and prev_g . y_a for the current history
   int hist_len = 0;
-  double* d_red = nullptr;       // reduction banks
-  double* h_vals = nullptr;      // pinned: the values that the host reads, written by the device
+  double* d_red = nullptr;       // reduction banks, then a value per bank (used without h_vals)
+  double* h_vals = nullptr;      // pinned: the values that the host reads, written by the device (null: none left)
   // settings
   double lr = 1.0, tol_grad = 1e-7, tol_change = 1e-9;
   int history = 10, max_iter = 20, max_eval = 25;
@@ -56,13 +56,15 @@ int l2_box_copy_any(fe_l2* L, const void* src, void* dst, int to_padded) {
 // and 4 |g|_1 (first iteration); then the inner products of the Gram pass
 // (y.y, y.s, y.g, g.g, g.s, then g.V_k for each history vector). d_red
 // holds one bank of kVecBlocks partials per slot; the values go to pinned host
-// memory, one per slot (the sweep's finish writes the energy there directly).
+// memory, one per slot (the sweep's finish writes the energy there directly), or
+// behind the banks where there was none, and are copied.
 constexpr int kSlotE = 0, kSlotGmax = 1, kSlotDmax = 2, kSlotGtd = 3, kSlotL1 = 4, kSlotGram = 5;
 constexpr int kL2MaxHistory = 64;
 constexpr int kL2Banks = kSlotGram + 5 + 2 * kL2MaxHistory;
-constexpr size_t kL2RedDoubles = (size_t)kL2Banks * fe::kVecBlocks;
+constexpr size_t kL2RedDoubles = (size_t)kL2Banks * fe::kVecBlocks + kL2Banks;
 
 double* l2_bank(fe_l2* L, int slot) { return L->d_red + (size_t)slot * fe::kVecBlocks; }
+double* l2_vals(fe_l2* L) { return L->h_vals ? L->h_vals : l2_bank(L, kL2Banks); }
 
 const dim3 kVecGrid(fe::kVecBlocks), kVecBlock(fe::kVecThreads);
 
@@ -89,12 +91,14 @@ int l2_reduce_dev(fe_l2* L, int op, const void* a, const void* b, int slot) {
 int l2_read_slots(fe_l2* L, int count, double* out) {
   if (count > kSlotGmax) {
     hipLaunchKernelGGL(fe::vec_finish, dim3(count - kSlotGmax), dim3(64), 0, L->ctx->stream,
-                       (const double*)l2_bank(L, kSlotGmax), L->h_vals + kSlotGmax,
+                       (const double*)l2_bank(L, kSlotGmax), l2_vals(L) + kSlotGmax,
                        (1u << (kSlotGmax - kSlotGmax)) | (1u << (kSlotDmax - kSlotGmax)));
     FE_HIP(hipGetLastError());
   }
+  if (!L->h_vals)
+    FE_HIP(hipMemcpyAsync(out, l2_vals(L), sizeof(double) * count, hipMemcpyDeviceToHost, L->ctx->stream));
   FE_HIP(hipStreamSynchronize(L->ctx->stream));
-  std::copy_n(L->h_vals, count, out);
+  if (L->h_vals) std::copy_n(L->h_vals, count, out);
   return FE_OK;
 }
 
@@ -248,7 +252,7 @@ int l2_eval_dev(fe_l2* L, T* g, const fe::EdgeBox& eo) {
     l2_blur<T, fe::kReplicate>(L, x, w0, w1, w2, l2_edge(L));   // w2 = k * x
     ub = w2;
   }
-  int rc = sweep_energy(L->ctx, L->ctx->stream, fe::kGrad, ub, w0, L->h_vals + kSlotE);
+  int rc = sweep_energy(L->ctx, L->ctx->stream, fe::kGrad, ub, w0, l2_vals(L) + kSlotE);
   if (rc) return rc;
   if (L->r > 0) {
     l2_blur<T, fe::kAdjoint>(L, w0, w1, w2, g, eo);
@@ -529,10 +533,7 @@ int fe_l2_create(const fe_grid* grid, double eps, const double* p_coeffs, double
     l2_free(L);
     return set_error(FE_ENOMEM, "L2 flow reduction buffer allocation failed");
   }
-  if (!(L->h_vals = pinned_take(kL2Banks))) {
-    l2_free(L);
-    return set_error(FE_ENOMEM, "L2 flow result buffer allocation failed");
-  }
+  L->h_vals = pinned_take(kL2Banks);
   if (hipMemsetAsync(L->d_red, 0, sizeof(double) * kL2RedDoubles, c->stream) != hipSuccess) {
     l2_free(L);
     return set_error(FE_EHIP, "hipMemsetAsync failed");

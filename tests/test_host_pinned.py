@@ -4,7 +4,7 @@ back from the middle, requests around a unit's and the slab's ends, and none lef
 
 import ctypes
 
-from host_stub import dbl, run
+from host_stub import F64, HELFRICH_P, dbl, run
 
 SHAPE = (4, 8, 8)
 
@@ -72,9 +72,35 @@ def none_left(api):
     assert api.stub.stub_host_live() == 0
 
 
+def flow_with_none_left(api):
+    shape = (6, 8, 10)
+    logs = []
+    for full in (0, 1):
+        api.stub.stub_host_full(full)
+        L = ctypes.c_void_p()
+        rc = api.lib.fe_l2_create(ctypes.byref(api.grid(shape, F64)), ctypes.c_double(0.2), dbl(HELFRICH_P),
+                                  ctypes.c_double(1.0), None, ctypes.byref(L))
+        assert rc == 0, api.error()
+        u, E = api.field(shape), dbl([0.0])
+        for first in (3.0, 4.0):
+            api.stub.stub_next(first)
+            assert api.lib.fe_l2_energy_grad(L, u, api.field(shape), E) == 0 and E[0] == first
+        api.log()
+        Es = dbl([0.0] * 2)
+        assert api.lib.fe_l2_step(L, 2, Es) == 0 and list(Es) == [4.0, 4.0]
+        logs.append(api.log())
+        api.lib.fe_l2_destroy(L)
+        assert api.stub.stub_host_live() == 0
+    assert logs[0] == logs[1] and len(logs[0]) > 4    # the same iterations either way
+
+
 def test_more_contexts_than_the_slab_holds():
     run(full_slab)
 
 
 def test_no_pinned_memory():
     run(none_left)
+
+
+def test_flow_without_pinned_memory():
+    run(flow_with_none_left)
