@@ -133,8 +133,10 @@ int fe_grad_scaled_async(fe_ctx* ctx, const void* u, void* g, const double* gsca
  *               (not both NULL).
  *   stream      hipStream_t the work is ordered on (NULL: default stream).
  * Nothing synchronises; the launch shape is the one a fresh context would
- * choose. FE_EINVAL for a batch above 16, invalid parameters, or a grid whose
- * sweep needs more block partials than the array holds (65280; 256^3 needs 512).
+ * choose, with longer z chunks for a gradient where that one needs more block
+ * partials than the array holds (65280; 256^3 needs 768 at most). FE_EINVAL for a
+ * batch above 16, invalid parameters, or a grid with more tile columns than that
+ * (energy only: whose sweep needs more partials than that).
  * Every call on a device shares that device's array (the last call's contents
  * stay there; every value a call reads it has written first in stream order),
  * so calls that overlap on one device - on two streams, or from two host

@@ -494,8 +494,10 @@ int halo1_chunk(long cols, int nz, int num_cu, int slots) {
 }
 
 // `slots`: blocks of the launched kernel that one compute unit holds at once
-// (used when lz_req is 0, automatic).
-Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, int slots, int kind) {
+// (used when lz_req is 0, automatic). `most`: automatic chunks make no more blocks than
+// this where one chunk per tile column allows it.
+Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, int slots, int kind,
+                     long most = std::numeric_limits<long>::max()) {
   const Variant& v = variants()[variant];
   Geometry g;
   g.ntx = ceil_div(grid.nx, v.tx);
@@ -514,6 +516,7 @@ Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, i
       const int l = ceil_div(nz, nzc);
       if (nzc > 1 && l == ceil_div(nz, nzc - 1)) continue;   // the same chunks as nzc - 1
       const long blocks = cols * ceil_div(nz, l);
+      if (nzc > 1 && blocks > most) break;
       const double t = kind == fe::kGrad
                            ? sweep_cost(blocks, num_cu, std::min(slots, kGradSlots), l + kGradExtra, kGradShare)
                            : sweep_cost(blocks, num_cu, slots, l + 2);

@@ -73,12 +73,13 @@ int noalloc_sweep(const fe_grid& grid, const double* eps, const double* a, const
   const Variant& v = variants()[vi];
   const Kernels<T>& k = kernels_of<T>(v, false);
   const SweepFn<T> fn = sweep_kernel<T>(k, fe::kGrad, batch_body(pack.p, grid.batch));
-  // z chunks from the blocks per compute unit of the kernel launched, as in a context
+  // z chunks from the blocks per compute unit of the kernel launched, as in a context, but
+  // no more of them than the scratch holds partials for (grids thin in x or y and long in z)
   int slots = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&slots, (const void*)fn, v.nt, 0) != hipSuccess || slots < 1)
     slots = 1;
-  const Geometry geo =
-      g ? geometry_of(grid, slot.num_cu, vi, 0, slots, fe::kGrad) : energy_geometry(grid, slot.num_cu);
+  const Geometry geo = g ? geometry_of(grid, slot.num_cu, vi, 0, slots, fe::kGrad, (long)kScratchPartials)
+                         : energy_geometry(grid, slot.num_cu);
   const size_t nblocks = (size_t)geo.per_inst * grid.batch;
   if (nblocks > kScratchPartials)
     return set_error(FE_EINVAL, "grid needs %zu block partials; the static scratch holds %zu", nblocks,

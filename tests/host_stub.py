@@ -35,7 +35,7 @@ def run(fn, timeout=60):
             f"s = u.spec_from_file_location('cases', {fn.__code__.co_filename!r}); m = u.module_from_spec(s); "
             f"s.loader.exec_module(m); import host_stub; m.{fn.__name__}(host_stub.Api({_stub()!r}))")
     res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=timeout)
-    assert res.returncode == 0, res.stdout + res.stderr
+    assert res.returncode == 0, f"exit {res.returncode}: {res.stdout}{res.stderr}"
 
 
 class Grid(ctypes.Structure):

@@ -1,0 +1,32 @@
+"""What the allocation-free entry point and saved tuning files accept."""
+
+import ctypes
+
+from host_stub import ASYM_P, EINVAL, F32, F64, HELFRICH_P, TRACE_P, dbl, run
+
+
+def _noalloc(api, shape, p, dtype):
+    u, g = ctypes.c_void_p(4096), ctypes.c_void_p(8192)        # no kernel runs: the fields are never read
+    return api.lib.fe_energy_grad_noalloc(ctypes.byref(api.grid(shape, dtype)), dbl([2.0 / shape[2]]), dbl(p), u, g,
+                                          dbl([0.0]), None)
+
+
+def thin_grids(api):
+    """Grids with many tile columns and long in z, where the chunks that finish first need
+    more partials than the static array holds: taken in longer chunks. 2 to 16 blocks per
+    compute unit; 35667, 4462, 2319, 28906 and 31563 columns of 8 x 8 voxels."""
+    for slots in (2, 3, 8, 16):
+        api.stub.stub_slots(slots)
+        for dtype in (F32, F64):
+            for p in (TRACE_P, HELFRICH_P, ASYM_P):
+                for shape in ((438, 285336, 8), (12256, 35696, 8), (21811, 18552, 8), (2300, 231248, 7),
+                              (1485, 252504, 8)):
+                    api.log()
+                    assert _noalloc(api, shape, p, dtype) == 0, (slots, shape, api.error())
+                    blocks = [b for n, b in api.log() if "grad_sweep" in n]
+                    assert len(blocks) == 1 and blocks[0] <= 65280, (slots, shape, blocks)
+    assert _noalloc(api, (1, 8192, 8192), HELFRICH_P, F32) == EINVAL      # 65536 columns of 32 x 32
+
+
+def test_noalloc_takes_thin_grids():
+    run(thin_grids)
