@@ -1353,12 +1353,12 @@ int fe_autotune(fe_ctx* c, const void* u, void* work, int kind, int iters, doubl
   int flip = 0;
   auto launch = [&]() -> int {
     if (kind == FE_TUNE_GRAD) return fe_energy_grad_async(c, u, work, nullptr);
-    // one step on the copy (no mass shift: the same kernel, without the first
-    // wave's sum of its predecessor's partials)
+    // one step on the copy (no mass shift: the kernel of all steps of a call but the
+    // last, without the first wave's sum of its predecessor's partials)
     void* src = flip ? c->d_pingpong : work;
     void* dst = flip ? work : c->d_pingpong;
     flip ^= 1;
-    return sweep(c, c->stream, rule.mode, src, dst, nullptr, partials_buf(c, 0), rule, 0);
+    return sweep(c, c->stream, rule.mode, src, dst, nullptr, partials_buf(c, 0), rule, 0, false);
   };
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {

@@ -1,8 +1,8 @@
-"""What the allocation-free entry point and saved tuning files accept."""
+"""What the allocation-free entry point accepts, and what the autotuner times."""
 
 import ctypes
 
-from host_stub import ASYM_P, EINVAL, F32, F64, HELFRICH_P, TRACE_P, dbl, run
+from host_stub import ASYM_P, EINVAL, F32, F64, FULL, HELFRICH_P, NO_S, TRACE, TRACE_P, dbl, run
 
 
 def _noalloc(api, shape, p, dtype):
@@ -28,5 +28,29 @@ def thin_grids(api):
     assert _noalloc(api, (1, 8192, 8192), HELFRICH_P, F32) == EINVAL      # 65536 columns of 32 x 32
 
 
+def _autotune(api, ctx, shape, kind=1):
+    us, cached = ctypes.c_double(), ctypes.c_int()
+    u, work = api.field(shape), api.field(shape)
+    assert api.lib.fe_autotune(ctx, u, work, kind, 1, ctypes.byref(us), ctypes.byref(cached)) == 0, api.error()
+    return cached.value
+
+
+def tuned_sweeps(api):
+    """The tuner times what a loop runs: steps without the energy where a launch shape has
+    such a kernel (32 x 32 / 512 threads: the leading one), gradients with it."""
+    for p, body in ((TRACE_P, TRACE), (HELFRICH_P, NO_S), (ASYM_P, FULL)):
+        for kind in (0, 1, 2):
+            ctx = api.context((8, 32, 32), p)
+            api.lib.fe_tune_cache_clear()
+            api.log()
+            assert _autotune(api, ctx, (8, 32, 32), kind) == 0
+            lead = [(m, b, e) for m, b, e in api.sweeps() if b == body]
+            assert lead and all(s == (kind, body, kind == 0) for s in lead), (kind, body, set(lead))
+
+
 def test_noalloc_takes_thin_grids():
     run(thin_grids)
+
+
+def test_the_tuner_times_the_sweeps_that_run():
+    run(tuned_sweeps)
