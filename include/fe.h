@@ -335,10 +335,12 @@ enum fe_tune_kind { FE_TUNE_GRAD = 0, FE_TUNE_STEP = 1, FE_TUNE_ADAM = 2 };
 /*
  * Pick the launch shape (variant and z-chunk length) for the sweep that `kind`
  * names, and keep it in the context. The choice depends on the grid, batch,
- * dtype, kind, on whether the instances' p are symmetric in k1, k2 (which
- * per-voxel body the sweep holds), on a coefficient field or box mask, and on
- * the device architecture; a choice made earlier in this process for the same
- * key, or loaded by fe_tune_cache_load, is taken without timing (*cached = 1).
+ * dtype, kind, on whether the instances' p are symmetric in k1, k2 or functions
+ * of k1 + k2 alone (which per-voxel body the sweep holds), on a coefficient field
+ * or box mask, and on the device architecture; a choice made earlier in this
+ * process for the same key, or loaded by fe_tune_cache_load, is taken without
+ * timing (*cached = 1). For p of k1 + k2 alone a loaded choice for symmetric p
+ * (files saved before the two differed hold no other) is taken if there is none.
  * Otherwise the workload first runs 50 ms untimed (the clocks settle), then
  * every variant that supports the dtype is timed at a few z-chunk lengths,
  * `iters` launches each, and the fastest is kept and cached.

@@ -951,13 +951,14 @@ int run_steps(fe_ctx* c, void* u, const double* mass, const StepRule& rule, int 
 struct TuneEntry {
   int variant = 0, lz = 0;
   double us = 0.0;
+  bool loaded = false;   // from a file, not timed here
 };
 std::map<std::string, TuneEntry> g_tune_cache;
 std::mutex g_tune_mu;
 
 // "<nx>x<ny>x<nz>x<batch>:<f32|f64>:<grad|step|adam>:<body>:<field|box|->:<device arch>"
-// (the key holds no spaces).
-int tune_key(const fe_ctx* c, int kind, std::string& key) {
+// (the key holds no spaces), with the context's body or another one.
+int tune_key(const fe_ctx* c, int kind, int body, std::string& key) {
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, c->device) != hipSuccess)
     return set_error(FE_EHIP, "hipGetDeviceProperties failed");
@@ -968,7 +969,7 @@ int tune_key(const fe_ctx* c, int kind, std::string& key) {
   static const char* bodies[] = {"any", "nos", "full", "trace"};
   char buf[320];
   std::snprintf(buf, sizeof(buf), "%dx%dx%dx%d:%s:%s:%s:%s:%s", c->grid.nx, c->grid.ny, c->grid.nz, c->grid.batch,
-                c->grid.dtype == FE_F32 ? "f32" : "f64", kinds[kind], bodies[c->body],
+                c->grid.dtype == FE_F32 ? "f32" : "f64", kinds[kind], bodies[body],
                 c->use_box ? "box" : c->use_cfield ? "field" : "-", arch.c_str());
   key = buf;
   return FE_OK;
@@ -980,6 +981,18 @@ bool tune_lookup(const std::string& key, TuneEntry& out) {
   if (it == g_tune_cache.end()) return false;
   out = it->second;
   return true;
+}
+
+// The choice kept for a context. A p of k1 + k2 alone had the body without S~ terms
+// before it had one of its own: a saved choice for that body still serves it, unless
+// there is one of its own.
+int tune_find(const fe_ctx* c, int kind, const std::string& key, TuneEntry& out, bool& found) {
+  found = tune_lookup(key, out);
+  if (found || c->body != fe::kBodyTrace) return FE_OK;
+  std::string nos;
+  const int rc = tune_key(c, kind, fe::kBodyNoS, nos);
+  found = !rc && tune_lookup(nos, out) && out.loaded;
+  return rc;
 }
 
 void tune_store(const std::string& key, const TuneEntry& e) {
@@ -1299,10 +1312,12 @@ int fe_autotune(fe_ctx* c, const void* u, void* work, int kind, int iters, doubl
   DeviceGuard dg(c->device);
   if (cached) *cached = 0;
   std::string key;
-  int rc = tune_key(c, kind, key);
-  if (rc) return rc;
+  int rc = tune_key(c, kind, c->body, key);
   TuneEntry hit;
-  if (tune_lookup(key, hit)) {
+  bool found = false;
+  if (!rc) rc = tune_find(c, kind, key, hit, found);
+  if (rc) return rc;
+  if (found) {
     c->variant = hit.variant;
     c->lz = hit.lz;
     if (best_us) *best_us = hit.us;
@@ -1456,6 +1471,7 @@ int fe_tune_cache_load(const char* path) {
       rc = set_error(FE_EINVAL, "%s:%d: not a tuning record", path, lineno);
       break;
     }
+    e.loaded = true;
     got[key] = e;
   }
   std::fclose(f);

@@ -1,6 +1,9 @@
-"""What the allocation-free entry point accepts, and what the autotuner times."""
+"""What the allocation-free entry point and saved tuning files accept, and what the
+autotuner times."""
 
 import ctypes
+import os
+import tempfile
 
 from host_stub import ASYM_P, EINVAL, F32, F64, FULL, HELFRICH_P, NO_S, TRACE, TRACE_P, dbl, run
 
@@ -35,6 +38,34 @@ def _autotune(api, ctx, shape, kind=1):
     return cached.value
 
 
+def saved_choices(api):
+    """A record saved before sweeps of a p in k1 + k2 alone had a body of their own serves
+    such a context as it did; a record of its own goes first; choices timed in this process
+    for another body are not taken."""
+    shape = (8, 32, 32)
+    path = os.path.join(tempfile.mkdtemp(), "tune.txt").encode()
+    record = "32x32x8x1:f32:step:{}:-:stub {} {} 9.0\n"
+    variant, z = ctypes.c_int(), ctypes.c_int()
+
+    def launch(ctx):
+        assert api.lib.fe_get_launch(ctx, ctypes.byref(variant), ctypes.byref(z)) == 0
+        return variant.value, z.value
+
+    for records, want in ((record.format("nos", 2, 4), (2, 4)),
+                          (record.format("nos", 2, 4) + record.format("trace", 3, 2), (3, 2))):
+        open(path, "w").write(records)
+        api.lib.fe_tune_cache_clear()
+        assert api.lib.fe_tune_cache_load(path) == 0
+        ctx = api.context(shape, TRACE_P)
+        assert _autotune(api, ctx, shape) == 1 and launch(ctx) == want
+        assert _autotune(api, api.context(shape, HELFRICH_P), shape) == 1
+        assert _autotune(api, api.context(shape, ASYM_P), shape) == 0
+    api.lib.fe_tune_cache_clear()
+    assert _autotune(api, api.context(shape, HELFRICH_P), shape) == 0
+    assert _autotune(api, api.context(shape, TRACE_P), shape) == 0
+    assert _autotune(api, api.context(shape, TRACE_P), shape) == 1
+
+
 def tuned_sweeps(api):
     """The tuner times what a loop runs: steps without the energy where a launch shape has
     such a kernel (32 x 32 / 512 threads: the leading one), gradients with it."""
@@ -50,6 +81,10 @@ def tuned_sweeps(api):
 
 def test_noalloc_takes_thin_grids():
     run(thin_grids)
+
+
+def test_saved_choices_serve_the_bodies_they_did():
+    run(saved_choices)
 
 
 def test_the_tuner_times_the_sweeps_that_run():
