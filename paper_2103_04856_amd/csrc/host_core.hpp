@@ -466,14 +466,19 @@ double sweep_cost(long blocks, int num_cu, int slots, int L, double share = 0.6)
 
 // The same model for the gradient sweeps: the planes that a chunk of l costs beyond
 // its own, the share's exponent and the most slots counted (the trace body fits four
-// blocks, but is near its memory rate with three). Fitted to 72 gradient sweeps, three
-// bodies, both precisions, 64^3 to 600 x 100 x 100 and 1 to 16 instances, over all
-// chunk lengths: the chosen one costs 0.25 % (trace body 1.1 %) more than the best one
-// on average; 2 planes, 0.6 and every slot cost 0.4 % (2.2 %). 16 x 100^3 FP32 without
-// S terms: 25 planes, 85.8 us, against 13 and 94.0; 160 x 224 x 160, trace body: 12
-// and 25.1 against 6 and 27.3. The steps keep their chunks: their mass sums follow them.
-constexpr int kGradExtra = 3, kGradSlots = 3;
+// blocks of 512 threads, but is near its memory rate with three). Fitted to 72 gradient
+// sweeps in such blocks, three bodies, both precisions, 64^3 to 600 x 100 x 100 and 1 to
+// 16 instances, over all chunk lengths: the chosen one costs 0.25 % (trace body 1.1 %)
+// more than the best one on average; 2 planes, 0.6 and every slot cost 0.4 % (2.2 %).
+// 16 x 100^3 FP32 without S terms: 25 planes, 85.8 us, against 13 and 94.0; 160 x 224 x
+// 160, trace body: 12 and 25.1 against 6 and 27.3. Three blocks of 512 are 24 waves;
+// smaller blocks count as many waves: three blocks of 64 would leave a compute unit
+// nearly idle (100 x 10^3 FP32: 17.5 us, with 24 slots 11.5; 64 x 20^3 with a
+// coefficient field: 36.7 and 19.7). The steps keep their chunks: their mass sums
+// follow them.
+constexpr int kGradExtra = 3;
 constexpr double kGradShare = 0.5;
+int grad_slots(int threads) { return 3 * std::max(1, 512 / threads); }
 
 // The z chunk length of a halo-1 sweep (the energy-only and diagnostics sweeps)
 // over `cols` tile columns that sweep_cost finishes first, a chunk of l planes
@@ -518,7 +523,7 @@ Geometry geometry_of(const fe_grid& grid, int num_cu, int variant, int lz_req, i
       const long blocks = cols * ceil_div(nz, l);
       if (nzc > 1 && blocks > most) break;
       const double t = kind == fe::kGrad
-                           ? sweep_cost(blocks, num_cu, std::min(slots, kGradSlots), l + kGradExtra, kGradShare)
+                           ? sweep_cost(blocks, num_cu, std::min(slots, grad_slots(v.nt)), l + kGradExtra, kGradShare)
                            : sweep_cost(blocks, num_cu, slots, l + 2);
       if (lz <= 0 || t < best) {
         best = t;
