@@ -471,14 +471,16 @@ double sweep_cost(long blocks, int num_cu, int slots, int L, double share = 0.6)
 // 16 instances, over all chunk lengths: the chosen one costs 0.25 % (trace body 1.1 %)
 // more than the best one on average; 2 planes, 0.6 and every slot cost 0.4 % (2.2 %).
 // 16 x 100^3 FP32 without S terms: 25 planes, 85.8 us, against 13 and 94.0; 160 x 224 x
-// 160, trace body: 12 and 25.1 against 6 and 27.3. Three blocks of 512 are 24 waves;
-// smaller blocks count as many waves: three blocks of 64 would leave a compute unit
-// nearly idle (100 x 10^3 FP32: 17.5 us, with 24 slots 11.5; 64 x 20^3 with a
-// coefficient field: 36.7 and 19.7). The steps keep their chunks: their mass sums
+// 160, trace body: 12 and 25.1 against 6 and 27.3. In blocks of 64 to 256 threads 20
+// waves are counted (38 grids of 6 to 31 samples in x or y, three bodies and a
+// coefficient field, both precisions, over all chunk lengths: 1.7 % more than the best
+// chunk on average; 24 waves cost 2.2 %, 16 2.1 %; three such blocks would leave a
+// compute unit nearly idle: 100 x 10^3 FP32 17.5 us against 11.4, 64 x 20^3 with a
+// coefficient field 36.7 against 19.7). The steps keep their chunks: their mass sums
 // follow them.
 constexpr int kGradExtra = 3;
 constexpr double kGradShare = 0.5;
-int grad_slots(int threads) { return 3 * std::max(1, 512 / threads); }
+int grad_slots(int threads) { return threads >= 512 ? 3 : 20 * 64 / threads; }
 
 // The z chunk length of a halo-1 sweep (the energy-only and diagnostics sweeps)
 // over `cols` tile columns that sweep_cost finishes first, a chunk of l planes

@@ -30,5 +30,19 @@ def small_blocks(api):
                 api.lib.fe_destroy(ctx)
 
 
+def full_occupancy(api):
+    """Where 24 blocks of 64 threads fit a compute unit, 20 are counted: 300 grids of 10^3
+    in 8 x 8 tiles take two chunks, not five (16 and 18.7 us)."""
+    api.stub.stub_slots(24)
+    ctx = api.context((10, 10, 10), HELFRICH_P, F32, 300)
+    api.log()
+    assert api.lib.fe_energy_grad_async(ctx, api.field((300, 10, 10), 10), ctypes.c_void_p(8), None) == 0
+    assert [b for n, b in api.log() if "grad_sweep" in n] == [2400]
+
+
 def test_small_blocks_fill_the_chip():
     run(small_blocks)
+
+
+def test_small_blocks_at_full_occupancy():
+    run(full_occupancy)
