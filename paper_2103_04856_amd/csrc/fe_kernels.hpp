@@ -468,7 +468,16 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad
   const size_t inst_off = (size_t)bt.inst * a.nz * plane;
   const T* srcb = a.src + inst_off;
   T* dstb = a.dst + inst_off;
-  const InstParams<T> prm = a.prm[bt.inst];
+  InstParams<T> prm = a.prm[bt.inst];
+  // Adam steps that hold the body with the S~ terms run out of scalar registers, in FP64
+  // and in small blocks, and the table's multiples spill them to vector lanes (FP64: 115
+  // lane reads in the kernel instead of 31). Formed here (exact), they are vector values,
+  // which these kernels have to spare. 20 steps, with and without: 256^3 FP64 5948 and
+  // 6466 us, 200 x (12 x 20 x 9) FP32 427 and 469; in 512-thread FP32 blocks 4525 and 4434
+  // (16 x 128^3, mixed bodies).
+  if constexpr (MODE == kStepAdam && !SP &&
+                (sizeof(T) == 8 ? BODY == kBodyAny || BODY == kBodyFull : BODY == kBodyAny && NT < 512))
+    set_multiples(prm);
   // Adam bias corrections 1/(1 - beta^t)
   T bc1 = T(1), bc2 = T(1);
   if (MODE == kStepAdam) {
