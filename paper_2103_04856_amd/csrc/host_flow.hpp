@@ -108,12 +108,18 @@ template <typename T, int AXIS, int EDGE = fe::kPeriodic>
 void blur_axis_pass(hipStream_t s, const fe::FieldDims& d, const fe::BlurTaps<T>& k, const T* in, T* out,
                     const fe::EdgeBox& e = {}) {
   const dim3 g = axis_grid(pass_dims<EDGE>(d, e), AXIS), b(256);
-  if (k.r == 4)
-    hipLaunchKernelGGL((fe::blur_axis<T, AXIS, 4, EDGE>), g, b, 0, s, in, out, d, k, e);
-  else if (k.r == 8)
-    hipLaunchKernelGGL((fe::blur_axis<T, AXIS, 8, EDGE>), g, b, 0, s, in, out, d, k, e);
-  else
-    hipLaunchKernelGGL((fe::blur_axis<T, AXIS, -1, EDGE>), g, b, 0, s, in, out, d, k, e);
+  // with a box the y pass serves the radii without an x-y pass only
+  if constexpr (EDGE == fe::kPeriodic || AXIS == 2) {
+    if (k.r == 4) {
+      hipLaunchKernelGGL((fe::blur_axis<T, AXIS, 4, EDGE>), g, b, 0, s, in, out, d, k, e);
+      return;
+    }
+    if (k.r == 8) {
+      hipLaunchKernelGGL((fe::blur_axis<T, AXIS, 8, EDGE>), g, b, 0, s, in, out, d, k, e);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((fe::blur_axis<T, AXIS, -1, EDGE>), g, b, 0, s, in, out, d, k, e);
 }
 
 // out = k * f along y then z, through `tmp` (f is left as it was; out may be f).
