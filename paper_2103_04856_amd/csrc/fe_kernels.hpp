@@ -670,12 +670,12 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<T, NT, MODE, SP>())) void grad
   int sm = 0, sc = 1, sp = 2;                  // slots of p-1, p, p+1
   int pf = axis_index(k0 + 1, a.nz, 2);        // plane p + 2, wrapped (advanced by one per plane)
   start_priority();
-  // not peeled: in small blocks the compiler would run the first two planes (no output
-  // yet) from a copy of the body ahead of the loop, whose other FMA contractions make the
-  // results depend on the z chunk (and the Adam steps with both bodies spill scalars:
-  // 32 x 8 tiles, 2 x 100^3 FP32, 20 steps: 806 us, peeled 974)
-#pragma nounroll
   for (int it = 0; it < nit; ++it) {
+    // Not peeled: in blocks of small tiles, FP32, the compiler would run the first two planes (no
+    // output yet) of the sweeps that hold both bodies from a copy of the body ahead of the
+    // loop, whose other FMA contractions make the results depend on the z chunk (and the
+    // Adam steps spill scalars: 32 x 8 tiles, 2 x 100^3 FP32, 20 steps: 806 us, peeled 974)
+    if constexpr (sizeof(T) == 4 && NO == 1 && BODY == kBodyAny) __asm__("" : "+s"(it));
     const int p = k0 - 1 + it;
     progress_priority(it, nit);
     stage(sp);

@@ -460,7 +460,7 @@ double sweep_cost(long blocks, int num_cu, int slots, int L, double share = 0.6)
   const long k = (blocks + num_cu - 1) / num_cu;
   const long rest = k % slots;
   double t = (double)(k / slots) * L;
-  if (rest) t += L * std::pow((double)rest / slots, share);
+  if (rest) t += L * (share == 0.5 ? std::sqrt((double)rest / slots) : std::pow((double)rest / slots, share));
   return t;
 }
 
