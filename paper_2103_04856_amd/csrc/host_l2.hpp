@@ -24,7 +24,7 @@ struct fe_l2 {
   std::vector<double> SY, YY;    // [history][history]: s_a . y_b (a <= b) and y_a . y_b of the history
   std::vector<double> pgS, pgY;  // prev_g . s_a and prev_g . y_a for the current history
   int hist_len = 0;
-  double* d_red = nullptr;       // reduction banks, then a value per bank (used without h_vals)
+  double* d_red = nullptr;       // reduction banks
   double* h_vals = nullptr;      // pinned: the values that the host reads, written by the device (null: none left)
   // settings
   double lr = 1.0, tol_grad = 1e-7, tol_change = 1e-9;
@@ -56,15 +56,16 @@ int l2_box_copy_any(fe_l2* L, const void* src, void* dst, int to_padded) {
 // and 4 |g|_1 (first iteration); then the inner products of the Gram pass
 // (y.y, y.s, y.g, g.g, g.s, then g.V_k for each history vector). d_red
 // holds one bank of kVecBlocks partials per slot; the values go to pinned host
-// memory, one per slot (the sweep's finish writes the energy there directly), or
-// behind the banks where there was none, and are copied.
+// memory, one per slot (the sweep's finish writes the energy there directly); where
+// there was none, to the bank of kSlotE, which holds no partials, and are copied.
 constexpr int kSlotE = 0, kSlotGmax = 1, kSlotDmax = 2, kSlotGtd = 3, kSlotL1 = 4, kSlotGram = 5;
 constexpr int kL2MaxHistory = 64;
 constexpr int kL2Banks = kSlotGram + 5 + 2 * kL2MaxHistory;
-constexpr size_t kL2RedDoubles = (size_t)kL2Banks * fe::kVecBlocks + kL2Banks;
+constexpr size_t kL2RedDoubles = (size_t)kL2Banks * fe::kVecBlocks;
+static_assert(kL2Banks <= fe::kVecBlocks, "a value per slot in the bank of kSlotE");
 
 double* l2_bank(fe_l2* L, int slot) { return L->d_red + (size_t)slot * fe::kVecBlocks; }
-double* l2_vals(fe_l2* L) { return L->h_vals ? L->h_vals : l2_bank(L, kL2Banks); }
+double* l2_vals(fe_l2* L) { return L->h_vals ? L->h_vals : l2_bank(L, kSlotE); }
 
 const dim3 kVecGrid(fe::kVecBlocks), kVecBlock(fe::kVecThreads);
 
