@@ -717,8 +717,8 @@ def main():
         log("256^3 with a general p (S terms): energy+gradient sweep and Adam steps ...")
         gsw, gsa, gv, gzc = bench_general(n, args.steps)
         gvi = fe.variants()[gv]
-        ak = f"grad_sweep<float,{gvi[0]},{gvi[1]},{gvi[2]},2,false,false,2>"
-        gk = f"grad_sweep<float,{gvi[0]},{gvi[1]},{gvi[2]},0,false,false,2>"
+        ak = f"grad_sweep<float,{gvi[0]},{gvi[1]},{gvi[2]},2,false,false,2,false>"
+        gk = f"grad_sweep<float,{gvi[0]},{gvi[1]},{gvi[2]},0,false,false,2,true>"
         aroof, _ = roofline(FLOPS_PER_VOXEL + FLOPS_ADAM_EXTRA, BYTES_PER_VOXEL_ADAM, vox, gsa["median_us"], ak,
                             measured_traffic(ak, gzc))
         sroof, _ = roofline(FLOPS_PER_VOXEL, BYTES_PER_VOXEL_GRAD, vox, gsw["median_us"], gk,
@@ -734,10 +734,10 @@ def main():
         b_spread, bg_spread, s_spread, (bvar, bzc) = bench_batched(128, 16, args.warmup, args.tune)
         vb = 16 * 128 ** 3
         bv = fe.variants()[bvar]
-        bk = f"grad_sweep<float,{bv[0]},{bv[1]},{bv[2]},2,false,false,2>"
+        bk = f"grad_sweep<float,{bv[0]},{bv[1]},{bv[2]},2,false,false,2,false>"
         broof, bother = roofline(FLOPS_PER_VOXEL + FLOPS_ADAM_EXTRA, BYTES_PER_VOXEL_ADAM, vb,
                                  b_spread["median_us"], bk, measured_traffic(bk, bzc))
-        gk = f"grad_sweep<float,{bv[0]},{bv[1]},{bv[2]},0,false,false,2>"
+        gk = f"grad_sweep<float,{bv[0]},{bv[1]},{bv[2]},0,false,false,2,true>"
         groof, _ = roofline(FLOPS_PER_VOXEL, BYTES_PER_VOXEL_GRAD, vb, bg_spread["median_us"], gk,
                             measured_traffic(gk, bzc))
         extra["batched_16x128"] = {
@@ -760,13 +760,13 @@ def main():
         other_workloads(args, extra, n, vox)
 
     vinfo = fe.variants()[variant]
-    kname = f"grad_sweep<float,{vinfo[0]},{vinfo[1]},{vinfo[2]},1,false,false,1>"
+    kname = f"grad_sweep<float,{vinfo[0]},{vinfo[1]},{vinfo[2]},1,false,false,1,false>"
     roof, other = roofline(flops_per_voxel(HELFRICH_SC), BYTES_PER_VOXEL_STEP, vox, ms_step * 1e3, kname,
                            measured_traffic(kname, zc))
     ek = "energy_sweep_cols<float,2,8>"
     eroof, eother = roofline(forward_flops_per_voxel(HELFRICH_SC), BYTES_PER_VOXEL_ENERGY, vox,
                              single["energy"]["median_us"], ek, measured_traffic(ek, None))
-    gk = f"grad_sweep<float,{vinfo[0]},{vinfo[1]},{vinfo[2]},0,false,false,1>"
+    gk = f"grad_sweep<float,{vinfo[0]},{vinfo[1]},{vinfo[2]},0,false,false,1,true>"
     groof, _ = roofline(flops_per_voxel(HELFRICH_SC), BYTES_PER_VOXEL_GRAD, vox, single["grad"]["median_us"], gk,
                         measured_traffic(gk, zc))
 

@@ -379,8 +379,9 @@ __device__ __forceinline__ BlockTile block_tile(const SweepArgs<T>& a) {
 // density is not formed and partial [0] is 0.
 template <typename T, int NT, int MODE, bool SP>
 constexpr int sweep_min_waves() {
-  // two FP64 blocks of 512 threads share a compute unit with up to 128 registers;
-  // the gradient sweeps with the S~ terms would take 129 or 130
+  // two FP64 blocks of 512 threads share a compute unit with up to 128 registers; the
+  // gradient sweeps with the S~ terms would take 129 or 130 (capped, the one with that
+  // body alone and the energy keeps one register in scratch, 8 bytes per lane)
   return sizeof(T) == 8 && NT == 512 && MODE == kGrad && !SP ? 4 : 1;
 }
 

@@ -40,11 +40,10 @@ __global__ __launch_bounds__(256) void fold_shell(const T* __restrict__ g, T* __
 //
 // Every reduction runs on kVecBlocks blocks of kVecThreads threads and leaves
 // one FP64 partial per block in a bank of its own. The value of a reduction is
-// the combination of its bank in one fixed order (bank_value), formed where it
-// is needed: by every block of a later vector pass that takes it as a
-// coefficient, or by vec_finish for the host. No block waits for another and
-// no pass needs a device-wide fence, which on this GPU costs more than the
-// pass itself when every block issues one.
+// the combination of its bank in one fixed order (bank_value), which vec_finish
+// forms for the host. No block waits for another and no pass needs a device-wide
+// fence, which on this GPU costs more than the pass itself when every block
+// issues one.
 
 constexpr int kVecBlocks = 256;
 constexpr int kVecThreads = 1024;

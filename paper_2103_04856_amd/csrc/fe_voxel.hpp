@@ -249,8 +249,8 @@ __device__ __forceinline__ bool has_s_terms(const InstParams<T>& p) {
 // and their adjoints: seven samples instead of nineteen, 35 instead of 88
 // operations per voxel in the forward and reverse chain, four LDS fields instead
 // of seven. 256^3 FP32, p = (k1 + k2)^2 / 4, against the body without S~ terms:
-// energy + gradient 76.6 -> 48.8 us per call (2.8 TB/s of the 8 B/voxel),
-// energy only 30.8 -> 23.4 us (2.9 TB/s of the 4 B/voxel); 64^3 11.9 -> 11.1 us.
+// energy + gradient 76.9 -> 44.2 us per call (3.0 TB/s of the 8 B/voxel), energy
+// only 31.4 -> 22.3 us (3.0 TB/s of the 4 B/voxel); 64^3 calls wait for the host.
 template <typename T>
 __device__ __forceinline__ bool has_trace_only(const InstParams<T>& p) {
   return !has_s_terms(p) && p.C1 == T(0);

@@ -113,9 +113,10 @@ SweepFn<T> sweep_kernel(const Kernels<T>& k, int kind, int body, bool energy = t
   return !energy && quiet ? quiet : body_kernel<T>(k.fn[kind][0], body);
 }
 
-// Static LDS of grad_sweep is (4 (TX+4)(TY+4) + 7 (TX+2)(TY+2)) sizeof(T) plus
-// 16 bytes per wave; gfx950 allows up to 160 KiB per workgroup. The block size
-// need not divide the tile (the last round of a thread may be idle).
+// Static LDS of grad_sweep is three u planes of (TX+4)(TY+4) samples and seven adjoint
+// fields (the trace body four) of (TX+2)(TY+2), plus 16 bytes per wave; gfx950 allows up
+// to 160 KiB per workgroup. The block size need not divide the tile (the last round of a
+// thread may be idle).
 const std::vector<Variant>& variants() {
   static const std::vector<Variant> v = [] {
     std::vector<Variant> r;
@@ -130,8 +131,9 @@ const std::vector<Variant>& variants() {
       r.push_back(x);
     };
     // the coefficient-field and box kernels exist for a few large tiles, one
-    // small and the smallest tile of each precision (not for 50 x 20 with a
-    // coefficient field: 134 VGPRs, one block per CU). 32 x 32 and 50 x 20 lead
+    // small and the smallest tile of each precision (none for 50 x 20 with a
+    // coefficient field: it would take 108 to 123 VGPRs, two blocks per CU like the
+    // 64 x 16 one that serves such grids; not measured). 32 x 32 and 50 x 20 lead
     // the FP32 list: the same block (512 threads, three u loads and three ring
     // voxels per thread, 47 KiB of LDS, two or three blocks per CU) over a tile whose
     // ring is 1.13 or 1.14 of it. 32 x 32 covers power-of-two planes exactly,
